@@ -43,9 +43,7 @@ struct Ctrl {
   int32_t cg_done[2], cg_steps[2];
   uint64_t sel_bar[2];    // grid-barrier arrivals of the persistent selection
   uint64_t sel_barbase[2];
-  uint64_t cg_bar[2];     // grid-barrier arrivals of the persistent PCG
-  uint64_t cg_barbase[2]; // arrivals completed by earlier launches
-  int32_t sync_fail;      // a grid-barrier wait timed out
+  int32_t sync_fail;      // a wait between workgroups timed out
   int32_t pad0;
   unsigned ticket[8];     // last-block tickets (reset by the last block)
 };

@@ -290,21 +290,26 @@ struct CgWork {
   double *part = nullptr;    // 2 parities x 2 x part_cap (<r,zz>, <r,r>)
   int64_t part_cap = 0;      // cap/256 + 1
   double *rzs = nullptr;     // rz by step parity (2)
-  T *v2 = nullptr;           // persistent PCG: G p by step parity (2 * cap)
-  double *pv2 = nullptr;     // persistent PCG: <p, v> partials (2 * grid)
+  T *xch = nullptr;          // persistent PCG: G p, three buffers (3 * cap)
+  unsigned *seq = nullptr;   // persistent PCG: steps since they were cleared
 };
-// Persistent PCG (one launch per projection): largest Gram dimension and
-// grid size for a given dimension.
-int64_t pcg_persist_cap(bool f64);
+// Persistent PCG (one launch per projection, pcg.hip): whether a block
+// capacity fits it, and its grid.
+bool pcg_persist_fits(int64_t cap, int ncu, bool f64);
 int pcg_persist_grid(int64_t cap, int ncu);
+// Empties the exchange buffers: before the first launch of every solve (a
+// solve that failed may leave values behind).
 template <typename T>
-// F != nullptr: G has not been gathered; the first step reads the block
-// rows of the full Gram F (leading dimension ldf) through hlist and stores
-// them packed into G (cap x cap) for the later steps
+void launch_pcg_clear(CgWork<T> &w, hipStream_t st);
+// F != nullptr: G has not been gathered; the block's entries are read from
+// the full Gram F (leading dimension ldf) through hlist, and rows that do
+// not fit on the chip are stored packed into G (cap x cap).  nrm: the
+// diagonal of the full Gram (squared norms), the Jacobi preconditioner.
+template <typename T>
 void launch_pcg_persist(T *G, int64_t cap, const int64_t *count_dev,
-                        const T *hsrc, const int32_t *hlist, T *y,
-                        CgWork<T> &w, int grid, int max_steps, double tol,
-                        Ctrl *ctrl, int ph, int respect_done, hipStream_t st,
+                        const T *hsrc, const int32_t *hlist, const double *nrm,
+                        T *y, CgWork<T> &w, int grid, int max_steps,
+                        double tol, Ctrl *ctrl, int ph, hipStream_t st,
                         const T *F = nullptr, int64_t ldf = 0);
 // largest Gram dimension the PCG kernels accept (direction staged in LDS)
 int64_t pcg_cap_max();

@@ -506,205 +506,6 @@ void launch_pcg_gram_step(const T *G, int64_t cap, const int64_t *count_dev,
 }
 int64_t pcg_cap_max() { return PG_LDS_MAX; }
 
-// ------------------------------------------------------------ persistent PCG
-// The whole Jacobi-preconditioned CG of one block projection in one launch of
-// P co-resident workgroups (P <= compute units).  Workgroup w owns rows
-// [w*rpw, (w+1)*rpw) of G and of y.  Every workgroup keeps the full direction
-// p, residual res and diagonal of G in LDS and updates them redundantly
-// (O(c) work per step, identical bits in every workgroup); per step only the
-// product v = G p on the owned rows and a partial of <p, v> are exchanged,
-// through double-buffered global arrays and one grid barrier.  The stopping
-// test ||res|| <= tol ||h|| is evaluated identically by every workgroup, so
-// all leave the loop together.  The barrier waits are bounded: after
-// GRID_SPIN_MAX polls a workgroup raises Ctrl::sync_fail and leaves, so the
-// launch always drains.
-constexpr int PP_NT = 1024;                      // 16 waves: one row of G each
-constexpr int PP_RPW = 16;                       // rows of G per workgroup
-constexpr int PP_UNROLL = 8;                     // row loads in flight per lane
-template <typename T> struct PpCap;
-template <> struct PpCap<double> { static constexpr int64_t v = 4096; };
-template <> struct PpCap<float> { static constexpr int64_t v = 8192; };
-// 16-byte row loads of the packed block (rows start 16-byte aligned when
-// the leading dimension is a multiple of the vector width)
-typedef double pp_d2 __attribute__((ext_vector_type(2)));
-typedef float pp_f4 __attribute__((ext_vector_type(4)));
-template <typename T> struct PpVec;
-template <> struct PpVec<double> { using type = pp_d2; static constexpr int n = 2; };
-template <> struct PpVec<float> { using type = pp_f4; static constexpr int n = 4; };
-
-template <typename T>
-__global__ void __launch_bounds__(PP_NT)
-pcg_persist_kernel(T *__restrict__ G, int64_t ldg,
-                   const int64_t *__restrict__ cnt, const T *__restrict__ hsrc,
-                   const int32_t *__restrict__ hl, T *__restrict__ y,
-                   T *__restrict__ vbuf, double *__restrict__ pvbuf,
-                   int64_t cap, int max_steps, double tol, Ctrl *ctrl, int ph,
-                   int respect_done, const T *__restrict__ F, int64_t ldf) {
-  if (respect_done && ctrl_done(ctrl)) return;
-  constexpr int64_t CAP = PpCap<T>::v;
-  __shared__ T ps[CAP], rs[CAP], dg[CAP];
-  __shared__ int32_t sl[CAP];
-  __shared__ double sh[PP_NT / WAVE];
-  const int64_t c = *cnt;
-  const int P = (int)gridDim.x;
-  const int64_t rpw = (c + P - 1) / P;
-  const int64_t r0 = (int64_t)blockIdx.x * rpw;
-  const int64_t r1 = r0 + rpw < c ? r0 + rpw : c;
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  double rz = 0.0, rr = 0.0;
-  // F != nullptr: G is not gathered yet.  Every workgroup reads its own
-  // rows of the block straight from the full Gram F (the block list in
-  // LDS) during the first step and stores them packed for the later steps,
-  // which read only the rows the same threads wrote.
-  for (int64_t a = threadIdx.x; a < c; a += PP_NT) {
-    const T h = hl ? hsrc[hl[a]] : hsrc[a];
-    T d;
-    if (F) {
-      const int32_t l = hl[a];
-      sl[a] = l;
-      d = F[(int64_t)l * ldf + l];
-    } else {
-      d = G[a * ldg + a];
-    }
-    const T z = d > (T)0 ? h / d : (T)0;
-    rs[a] = h;
-    dg[a] = d;
-    ps[a] = z;
-    rz += (double)h * (double)z;
-    rr += (double)h * (double)h;
-  }
-  for (int64_t a = r0 + threadIdx.x; a < r1; a += PP_NT) y[a] = (T)0;
-  rz = block_sum<PP_NT>(rz, sh);
-  rr = block_sum<PP_NT>(rr, sh);
-  const double rr0 = rr;
-  const uint64_t base = ctrl->cg_barbase[ph];
-  int nbar = 0, t = 0;
-  bool run = !(rr0 == 0.0 || c == 0);
-  while (run && t < max_steps) {
-    const int par = t & 1;
-    T *vb = vbuf + (int64_t)par * cap;
-    double *pvb = pvbuf + (int64_t)par * P;
-    double pvp = 0.0;
-    for (int64_t row = r0 + wv; row < r1; row += PP_NT / WAVE) {
-      T *gr = G + row * ldg;
-      T s = (T)0;
-      int64_t b = lane;
-      if (F && t == 0) {
-        const T *fr = F + (int64_t)sl[row] * ldf;
-        for (; b + (PP_UNROLL - 1) * WAVE < c; b += PP_UNROLL * WAVE) {
-          T gv[PP_UNROLL];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u) gv[u] = fr[sl[b + u * WAVE]];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u) {
-            gr[b + u * WAVE] = gv[u];
-            s += gv[u] * ps[b + u * WAVE];
-          }
-        }
-        for (; b < c; b += WAVE) {
-          const T gv = fr[sl[b]];
-          gr[b] = gv;
-          s += gv * ps[b];
-        }
-      } else if (ldg % PpVec<T>::n == 0) {
-        using V = typename PpVec<T>::type;
-        constexpr int VN = PpVec<T>::n;
-        const V *grv = reinterpret_cast<const V *>(gr);
-        const int64_t cv = c / VN;
-        int64_t q = lane;
-        for (; q + (PP_UNROLL - 1) * WAVE < cv; q += PP_UNROLL * WAVE) {
-          V gv[PP_UNROLL];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u) gv[u] = grv[q + u * WAVE];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u)
-#pragma unroll
-            for (int v = 0; v < VN; ++v)
-              s += gv[u][v] * ps[(q + u * WAVE) * VN + v];
-        }
-        for (; q < cv; q += WAVE) {
-          const V g = grv[q];
-#pragma unroll
-          for (int v = 0; v < VN; ++v) s += g[v] * ps[q * VN + v];
-        }
-        for (b = cv * VN + lane; b < c; b += WAVE) s += gr[b] * ps[b];
-      } else {
-        for (; b + (PP_UNROLL - 1) * WAVE < c; b += PP_UNROLL * WAVE) {
-          T gv[PP_UNROLL];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u) gv[u] = gr[b + u * WAVE];
-#pragma unroll
-          for (int u = 0; u < PP_UNROLL; ++u) s += gv[u] * ps[b + u * WAVE];
-        }
-        for (; b < c; b += WAVE) s += gr[b] * ps[b];
-      }
-      s = wave_sum(s);
-      if (lane == 0) {
-        vb[row] = s;
-        pvp += (double)s * (double)ps[row];
-      }
-    }
-    pvp = block_sum<PP_NT>(pvp, sh);
-    if (threadIdx.x == 0) pvb[blockIdx.x] = pvp;
-    ++nbar;
-    if (!grid_barrier(&ctrl->cg_bar[ph], base + (uint64_t)nbar * P,
-                      &ctrl->sync_fail))
-      return;
-    double pv = 0.0;
-    for (int b = threadIdx.x; b < P; b += PP_NT) pv += ld_agent(&pvb[b]);
-    pv = block_sum<PP_NT>(pv, sh);
-    const double alpha = pv != 0.0 ? rz / pv : 0.0;
-    for (int64_t a = r0 + threadIdx.x; a < r1; a += PP_NT)
-      y[a] += (T)alpha * ps[a];
-    double rz1 = 0.0;
-    rr = 0.0;
-    for (int64_t a = threadIdx.x; a < c; a += PP_NT) {
-      const T r = rs[a] - (T)alpha * ld_agent(&vb[a]);
-      rs[a] = r;
-      const T z = dg[a] > (T)0 ? r / dg[a] : (T)0;
-      rz1 += (double)r * (double)z;
-      rr += (double)r * (double)r;
-    }
-    rz1 = block_sum<PP_NT>(rz1, sh);
-    rr = block_sum<PP_NT>(rr, sh);
-    ++t;
-    if (rr <= tol * tol * rr0 || rz == 0.0 || pv == 0.0) break;
-    const double beta = rz1 / rz;
-    rz = rz1;
-    for (int64_t a = threadIdx.x; a < c; a += PP_NT) {
-      const T z = dg[a] > (T)0 ? rs[a] / dg[a] : (T)0;
-      ps[a] = z + (T)beta * ps[a];
-    }
-    __syncthreads();
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ctrl->cg_barbase[ph] = base + (uint64_t)nbar * P;
-    ctrl->cg_steps[ph] = t;
-    ctrl->cg_done[ph] = 1;
-  }
-}
-
-int64_t pcg_persist_cap(bool f64) {
-  return f64 ? PpCap<double>::v : PpCap<float>::v;
-}
-int pcg_persist_grid(int64_t cap, int ncu) {
-  int64_t p = (cap + PP_RPW - 1) / PP_RPW;
-  if (p > ncu) p = ncu;
-  if (p < 1) p = 1;
-  return (int)p;
-}
-
-template <typename T>
-void launch_pcg_persist(T *G, int64_t cap, const int64_t *count_dev,
-                        const T *hsrc, const int32_t *hlist, T *y,
-                        CgWork<T> &w, int grid, int max_steps, double tol,
-                        Ctrl *ctrl, int ph, int respect_done, hipStream_t st,
-                        const T *F, int64_t ldf) {
-  hipLaunchKernelGGL(pcg_persist_kernel<T>, dim3(grid), dim3(PP_NT), 0, st, G,
-                     cap, count_dev, hsrc, hlist, y, w.v2, w.pv2, cap,
-                     max_steps, tol, ctrl, ph, respect_done, F, ldf);
-}
-
 // ------------------------------------------------------------ thin updates
 // out[i] (+)= sign * sum_a coef_a * M[list_a * ldm + i]: blockIdx.y takes a
 // chunk of UP_CHUNK list entries, each thread two consecutive i (one 16-byte
@@ -1764,11 +1565,6 @@ void launch_sparse_block_update(const Csr<T> &A, const int32_t *list,
   template void launch_pcg_gram_step<T>(const T *, int64_t, const int64_t *, \
                                         T *, CgWork<T> &, int, double,       \
                                         Ctrl *, int, int, hipStream_t);       \
-  template void launch_pcg_persist<T>(T *, int64_t, const int64_t *,         \
-                                      const T *, const int32_t *, T *,       \
-                                      CgWork<T> &, int, int, double, Ctrl *, \
-                                      int, int, hipStream_t, const T *,      \
-                                      int64_t);                               \
   template void launch_col_update<T>(const T *, int64_t, int64_t,            \
                                      const int32_t *, const int64_t *,       \
                                      int64_t, const T *, T *, T *, Ctrl *,   \

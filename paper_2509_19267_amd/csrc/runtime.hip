@@ -235,8 +235,8 @@ void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e) {
     cw->part_cap = cap / 256 + 2;
     cw->part = P.alloc<double>(4 * cw->part_cap);
     cw->rzs = P.alloc<double>(2);
-    cw->v2 = P.alloc<T>(2 * cap);
-    cw->pv2 = P.alloc<double>(2 * pcg_persist_grid(cap, h->ncu));
+    cw->xch = P.alloc<T>(3 * cap, false);
+    cw->seq = P.alloc<unsigned>(1);
   }
 }
 
@@ -636,25 +636,33 @@ struct IterOpts {
 };
 
 // Gram solve of a dense block projection: the persistent one-launch PCG when
-// the block fits its LDS staging, else two launches per CG step.  With a
+// the block fits it, else two launches per CG step.  With a
 // precomputed full Gram F (leading dimension ldf) the block G is not yet
-// gathered: the persistent PCG gathers it during its first step, the
-// step-per-launch form after a gather launch.
+// gathered: the persistent PCG reads it from F itself, the step-per-launch
+// form after a gather launch.  nrm: the full Gram's diagonal.
 template <typename T>
 void pcg_solve(rgdbek_ctx *h, T *G, int64_t cap, const int64_t *cnt,
-               const T *hsrc, const int32_t *hl, T *y, CgWork<T> &w, int maxs,
-               double itol, int ph, const T *F = nullptr, int64_t ldf = 0) {
+               const T *hsrc, const int32_t *hl, const double *nrm, T *y,
+               CgWork<T> &w, int maxs, double itol, int ph,
+               const T *F = nullptr, int64_t ldf = 0) {
   const bool f64 = std::is_same<T, double>::value;
-  if (cap <= pcg_persist_cap(f64)) {
-    launch_pcg_persist<T>(G, cap, cnt, hsrc, hl, y, w,
+  if (pcg_persist_fits(cap, h->ncu, f64)) {
+    launch_pcg_persist<T>(G, cap, cnt, hsrc, hl, nrm, y, w,
                           pcg_persist_grid(cap, h->ncu), maxs, itol, h->ctrl,
-                          ph, 1, h->st, F, ldf);
+                          ph, h->st, F, ldf);
     return;
   }
   if (F) launch_gram_gather<T>(F, ldf, hl, cnt, cap, G, h->ctrl, 1, h->st);
   launch_pcg_gram_init<T>(G, cap, cnt, hsrc, hl, y, w, h->ctrl, ph, 1, h->st);
   for (int k = 0; k < maxs; ++k)
     launch_pcg_gram_step<T>(G, cap, cnt, y, w, k, itol, h->ctrl, ph, 1, h->st);
+}
+
+// The persistent PCG's exchange buffers start every solve empty.
+template <typename T>
+void clear_exchange(Engine<T> &e, hipStream_t st) {
+  if (e.cgc.xch) launch_pcg_clear<T>(e.cgc, st);
+  if (e.cgr.xch) launch_pcg_clear<T>(e.cgr, st);
 }
 
 template <typename T>
@@ -720,7 +728,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     {
     ProfScope ps(h, RGDBEK_PROF_COL_SOLVE, 0);
     if (cg_c && e.ata) {
-      pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.y, e.cgc, maxs, itol, 0,
+      pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.kappa, e.y, e.cgc, maxs, itol, 0,
                    e.ata, e.n);
     } else {
       if (e.ata)
@@ -729,7 +737,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
         launch_gram_rows<T>(e.acm.a, e.acm.ld, e.m, e.U, cntU, e.kc, e.GU, c,
                             1, st);
       if (cg_c)
-        pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.y, e.cgc, maxs, itol, 0);
+        pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.kappa, e.y, e.cgc, maxs, itol, 0);
       else
         launch_chol_solve<T>(e.GU, e.kc, cntU, e.g, e.U, e.y, 1, c, 0, 1, st);
     }
@@ -741,7 +749,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     {
     ProfScope ps(h, RGDBEK_PROF_COL_SOLVE, 0);
     if (cg_c) {
-      pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.y, e.cgc, maxs, itol, 0,
+      pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.kappa, e.y, e.cgc, maxs, itol, 0,
                    e.ata, e.n);
     } else {
       launch_gram_gather<T>(e.ata, e.n, e.U, cntU, e.kc, e.GU, c, 1, st);
@@ -821,7 +829,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     if (!cg_r) {
       launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.r, e.J, e.w, 1, c, 1, 1, st);
     } else {
-      pcg_solve<T>(h, e.GJ, e.kr, cntJ, e.r, e.J, e.w, e.cgr, maxs, itol, 1,
+      pcg_solve<T>(h, e.GJ, e.kr, cntJ, e.r, e.J, e.rho, e.w, e.cgr, maxs, itol, 1,
                    e.aat, e.m);
     }
     }
@@ -845,7 +853,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     {
     ProfScope ps(h, RGDBEK_PROF_ROW_SOLVE, 1);
     if (cg_r) {
-      pcg_solve<T>(h, e.GJ, e.kr, cntJ, e.r, e.J, e.w, e.cgr, maxs, itol, 1,
+      pcg_solve<T>(h, e.GJ, e.kr, cntJ, e.r, e.J, e.rho, e.w, e.cgr, maxs, itol, 1,
                    e.aat, e.m);
     } else {
       launch_gram_gather<T>(e.aat, e.m, e.J, cntJ, e.kr, e.GJ, c, 1, st);
@@ -949,7 +957,7 @@ rgdbek_status finish_status(rgdbek_ctx *h, rgdbek_info *info, double secs,
   rgdbek_status s = RGDBEK_OK;
   if (c.sync_fail) {
     s = RGDBEK_ERR_DEVICE;
-    set_err(h, "a grid-barrier wait of the block solver timed out (the "
+    set_err(h, "a wait between workgroups of the block solver timed out (the "
                "workgroups of one launch were not all resident)");
   } else if (c.numeric) {
     s = RGDBEK_ERR_NUMERIC;
@@ -997,6 +1005,7 @@ rgdbek_status solve64(rgdbek_ctx *h, Engine<double> &e, int which,
   }
   check_b(h, b, e.m);
   prof_begin_solve(h);
+  clear_exchange(e, st);
   HIPCHK(hipMemcpyAsync(e.b, b, sizeof(double) * e.m, hipMemcpyDeviceToDevice, st));
   if (resume) {
     HIPCHK(hipMemcpyAsync(e.x, x, sizeof(double) * e.n, hipMemcpyDeviceToDevice, st));
@@ -1074,6 +1083,7 @@ rgdbek_status solve_mixed(rgdbek_ctx *h, const double *b, double *x,
   check_b(h, b, E.m);
   prof_begin_solve(h);
   HIPCHK(hipMemcpyAsync(E.b, b, sizeof(double) * E.m, hipMemcpyDeviceToDevice, st));
+  clear_exchange(F, st);
   launch_axpby<double, double>(E.n, 0.0, h->x64, 0.0, (const double *)nullptr, st);
   HIPCHK(hipMemcpyAsync(h->z64, b, sizeof(double) * E.m, hipMemcpyDeviceToDevice, st));
   if (E.nseg) {
