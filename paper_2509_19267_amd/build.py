@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "_lib")
 LIBNAME = "librgdbek.so"
 ARCH = "gfx950"
 
-SOURCES = ["select.hip", "spmv.hip", "proj.hip", "pcg.hip", "utils.hip", "batch.hip",
+SOURCES = ["select.hip", "spmv.hip", "proj.hip", "pcg.hip", "chol.hip", "utils.hip", "batch.hip",
            "rep.hip", "runtime.hip"]
 # Bit-exact selection needs unfused, correctly rounded FP64 operations.
 EXTRA = {"select.hip": ["-ffp-contract=off"]}
@@ -32,7 +32,7 @@ def hipcc():
 
 
 def common_flags():
-    return ["--offload-arch=" + ARCH, "-O3", "-fPIC", "-std=c++17",
+    return ["--offload-arch=" + ARCH, "-O3", "-fPIC", "-std=c++20",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-I" + os.path.join(HERE, "..", "include"), "-I" + CSRC]
 

@@ -271,14 +271,17 @@ template <typename T>
 void launch_gram_full(const T *X, int64_t ldx, int64_t rows, int64_t len,
                       T *F, hipStream_t st);
 
-// Cholesky factor of G (cap x cap storage, count from *count_dev) in place
-// and solve G y = h (h gathered through hlist from hsrc, or given).  One
-// workgroup; for counts up to CHOL_MAX.
+// Cholesky factor of G (cap x cap storage, count from *count_dev) and solve
+// of G y = h (h gathered through hlist from hsrc, or given); factor == 0: a
+// further solve with the factor of the last call on the same G and W.  One
+// workgroup; for counts up to CHOL_MAX.  W: chol_work_size(cap) entries of
+// work space (the factor of small blocks; larger ones are factored over G).
 constexpr int64_t CHOL_MAX = 512;
+int64_t chol_work_size(int64_t cap);
 template <typename T>
 void launch_chol_solve(T *G, int64_t cap, const int64_t *count_dev,
-                       const T *hsrc, const int32_t *hlist, T *y, int factor,
-                       Ctrl *ctrl, int ph, int respect_done, hipStream_t st);
+                       const T *hsrc, const int32_t *hlist, T *y, T *W,
+                       int factor, Ctrl *ctrl, hipStream_t st);
 
 // Preconditioned CG on the gathered Gram G y = h (Jacobi).  init + steps.
 template <typename T>

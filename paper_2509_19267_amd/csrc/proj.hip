@@ -18,6 +18,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "mfma16.h"
 
 namespace rg {
 
@@ -55,25 +56,7 @@ void launch_gram_gather(const T *F, int64_t ldf, const int32_t *list,
 // double-buffered LDS stages stored k-major (tile[k][row]), so the 16 lanes
 // that feed one MFMA row group read consecutive words; the next stage is
 // loaded from global memory into registers while the current one is
-// multiplied.  Operand layout of v_mfma_*_16x16x4 (both precisions): lane l
-// supplies A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator element r of
-// lane l is D[row(l / 16, r)][l % 16], row = 4 (l / 16) + r for FP32 and
-// 4 r + l / 16 for FP64 (measured on gfx950).
-template <typename T> struct Mfma16;
-template <> struct Mfma16<double> {
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 mma(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lk, int r) { return 4 * r + lk; }
-};
-template <> struct Mfma16<float> {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ v4 mma(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
-};
+// multiplied.
 constexpr int SY_B = 64;             // output tile (rows = columns)
 constexpr int SY_K = 16;             // k per LDS stage
 constexpr int SY_P = SY_B + 16;      // LDS row pitch (k-major rows of 64)
@@ -193,151 +176,6 @@ void launch_gram_full(const T *X, int64_t ldx, int64_t rows, int64_t len,
                      ldx, len, (const int32_t *)nullptr,
                      (const int64_t *)nullptr, rows, rows, F, (Ctrl *)nullptr,
                      0);
-}
-
-// ------------------------------------------------------------ Cholesky
-// One workgroup of 256 threads, blocked left-looking with 32-column panels
-// in LDS.  A pivot below 1e-13 of the largest diagonal marks the column as
-// dependent (its unknown is set to zero), which keeps the projection onto the
-// span of the block exact for rank-deficient blocks.
-constexpr int CNB = 32;
-constexpr int CNT = 256;
-
-template <typename T>
-__global__ void __launch_bounds__(CNT)
-chol_solve_kernel(T *__restrict__ G, int64_t ldg,
-                  const int64_t *__restrict__ cnt,
-                  const T *__restrict__ hsrc, const int32_t *__restrict__ hl,
-                  T *__restrict__ y, int factor, Ctrl *ctrl, int ph,
-                  int respect_done) {
-  if (respect_done && ctrl_done(ctrl)) return;
-  const int c = (int)*cnt;
-  if (c <= 0) return;
-  __shared__ T P[CHOL_MAX][CNB + 1];
-  __shared__ T Lb[CNB][CNB + 1];
-  __shared__ T vec[CHOL_MAX];
-  __shared__ T dmax;
-  const int tid = threadIdx.x;
-  if (factor) {
-    if (tid == 0) {
-      T mx = 0;
-      for (int i = 0; i < c; ++i) mx = G[(int64_t)i * ldg + i] > mx ? G[(int64_t)i * ldg + i] : mx;
-      dmax = mx;
-    }
-    __syncthreads();
-    const T thr = dmax * (T)1e-13;
-    for (int p = 0; p < c; p += CNB) {
-      const int w = (c - p) < CNB ? (c - p) : CNB;
-      const int h = c - p;
-      // load panel rows p..c-1, columns p..p+w-1
-      for (int e = tid; e < h * CNB; e += CNT) {
-        const int r = e / CNB, cc = e % CNB;
-        P[r][cc] = (cc < w) ? G[(int64_t)(p + r) * ldg + p + cc] : (T)0;
-      }
-      __syncthreads();
-      // left-looking update with previous panels: P -= L[p:, 0:p] L[p:p+w, 0:p]^T
-      for (int t0 = 0; t0 < p; t0 += CNB) {
-        for (int e = tid; e < CNB * CNB; e += CNT) {
-          const int rr = e / CNB, kk = e % CNB;
-          Lb[rr][kk] = (rr < w) ? G[(int64_t)(p + rr) * ldg + t0 + kk] : (T)0;
-        }
-        __syncthreads();
-        for (int r = tid; r < h; r += CNT) {
-          T lr[CNB];
-#pragma unroll
-          for (int kk = 0; kk < CNB; ++kk) lr[kk] = G[(int64_t)(p + r) * ldg + t0 + kk];
-          for (int cc = 0; cc < w && cc <= r; ++cc) {
-            T s = 0;
-#pragma unroll
-            for (int kk = 0; kk < CNB; ++kk) s += lr[kk] * Lb[cc][kk];
-            P[r][cc] -= s;
-          }
-        }
-        __syncthreads();
-      }
-      // factor the panel (right-looking inside LDS)
-      for (int j = 0; j < w; ++j) {
-        __syncthreads();
-        const T dj = P[j][j];
-        const bool dep = !(dj > thr);
-        const T sq = dep ? (T)0 : sqrt(dj);
-        __syncthreads();   // every wave has read the pivot before it changes
-        for (int r = j + tid; r < h; r += CNT) {
-          if (r == j) P[j][j] = sq;
-          else P[r][j] = dep ? (T)0 : P[r][j] / sq;
-        }
-        __syncthreads();
-        for (int r = j + 1 + tid; r < h; r += CNT) {
-          const T lrj = P[r][j];
-          const int kmax = r < w - 1 ? r : w - 1;
-          for (int k = j + 1; k <= kmax; ++k) P[r][k] -= lrj * P[k][j];
-        }
-      }
-      __syncthreads();
-      for (int e = tid; e < h * CNB; e += CNT) {
-        const int r = e / CNB, cc = e % CNB;
-        if (cc < w && cc <= r) G[(int64_t)(p + r) * ldg + p + cc] = P[r][cc];
-      }
-      __syncthreads();
-    }
-  }
-  // forward solve L v = h
-  for (int i = tid; i < c; i += CNT) vec[i] = hl ? hsrc[hl[i]] : hsrc[i];
-  __syncthreads();
-  for (int p = 0; p < c; p += CNB) {
-    const int w = (c - p) < CNB ? (c - p) : CNB;
-    // subtract contributions of solved entries 0..p-1 from rows p..p+w-1
-    if (tid < w) {
-      T s = 0;
-      for (int t = 0; t < p; ++t) s += G[(int64_t)(p + tid) * ldg + t] * vec[t];
-      vec[p + tid] -= s;
-    }
-    __syncthreads();
-    if (tid < WAVE) {
-      for (int j = 0; j < w; ++j) {
-        const T d = G[(int64_t)(p + j) * ldg + p + j];
-        T vj = vec[p + j];
-        vj = d != (T)0 ? vj / d : (T)0;
-        if (tid == 0) vec[p + j] = vj;
-        __builtin_amdgcn_wave_barrier();
-        if (tid > j && tid < w) vec[p + tid] -= G[(int64_t)(p + tid) * ldg + p + j] * vj;
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-  }
-  // backward solve L^T y = v
-  for (int p = ((c - 1) / CNB) * CNB; p >= 0; p -= CNB) {
-    const int w = (c - p) < CNB ? (c - p) : CNB;
-    if (tid < w) {
-      T s = 0;
-      for (int t = p + w; t < c; ++t) s += G[(int64_t)t * ldg + p + tid] * vec[t];
-      vec[p + tid] -= s;
-    }
-    __syncthreads();
-    if (tid < WAVE) {
-      for (int j = w - 1; j >= 0; --j) {
-        const T d = G[(int64_t)(p + j) * ldg + p + j];
-        T vj = vec[p + j];
-        vj = d != (T)0 ? vj / d : (T)0;
-        if (tid == 0) vec[p + j] = vj;
-        __builtin_amdgcn_wave_barrier();
-        if (tid < j) vec[p + tid] -= G[(int64_t)(p + j) * ldg + p + tid] * vj;
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    __syncthreads();
-  }
-  for (int i = tid; i < c; i += CNT) y[i] = vec[i];
-}
-
-template <typename T>
-void launch_chol_solve(T *G, int64_t cap, const int64_t *count_dev,
-                       const T *hsrc, const int32_t *hlist, T *y, int factor,
-                       Ctrl *ctrl, int ph, int respect_done, hipStream_t st) {
-  hipLaunchKernelGGL(chol_solve_kernel<T>, dim3(1), dim3(CNT), 0, st, G, cap,
-                     count_dev, hsrc, hlist, y, factor, ctrl, ph,
-                     respect_done);
 }
 
 // ------------------------------------------------------------ PCG on Gram
@@ -1555,9 +1393,6 @@ void launch_sparse_block_update(const Csr<T> &A, const int32_t *list,
                                     int64_t, T *, Ctrl *, int, hipStream_t);  \
   template void launch_gram_full<T>(const T *, int64_t, int64_t, int64_t,    \
                                     T *, hipStream_t);                        \
-  template void launch_chol_solve<T>(T *, int64_t, const int64_t *,          \
-                                     const T *, const int32_t *, T *, int,   \
-                                     Ctrl *, int, int, hipStream_t);          \
   template void launch_pcg_gram_init<T>(const T *, int64_t, const int64_t *, \
                                         const T *, const int32_t *, T *,     \
                                         CgWork<T> &, Ctrl *, int, int,        \

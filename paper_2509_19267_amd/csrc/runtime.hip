@@ -100,6 +100,7 @@ struct Engine {
   // dense block work
   DenseWork<T> dw;
   T *GU = nullptr, *GJ = nullptr, *y = nullptr, *w = nullptr, *s = nullptr;
+  T *chw = nullptr;           // work space of the Cholesky block solves
   T *upd = nullptr;
   CgWork<T> cgc, cgr;
   // sparse block work
@@ -221,6 +222,7 @@ void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e) {
   Pool &P = h->pool;
   e.GU = P.alloc<T>(e.kc * e.kc);
   if (!e.tall_rows) e.GJ = P.alloc<T>(e.kr * e.kr);
+  e.chw = P.alloc<T>(std::max(chol_work_size(e.kc), chol_work_size(e.kr)), false);
   e.y = P.alloc<T>(e.kc);
   e.w = P.alloc<T>(e.kr);
   e.s = P.alloc<T>(e.kr);
@@ -739,7 +741,8 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
       if (cg_c)
         pcg_solve<T>(h, e.GU, e.kc, cntU, e.g, e.U, e.kappa, e.y, e.cgc, maxs, itol, 0);
       else
-        launch_chol_solve<T>(e.GU, e.kc, cntU, e.g, e.U, e.y, 1, c, 0, 1, st);
+        launch_chol_solve<T>(e.GU, e.kc, cntU, e.g, e.U, e.y, e.chw, 1, c,
+                             st);
     }
     }
     ProfScope pu(h, RGDBEK_PROF_COL_UPDATE);
@@ -753,7 +756,8 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
                    e.ata, e.n);
     } else {
       launch_gram_gather<T>(e.ata, e.n, e.U, cntU, e.kc, e.GU, c, 1, st);
-      launch_chol_solve<T>(e.GU, e.kc, cntU, e.g, e.U, e.y, 1, c, 0, 1, st);
+      launch_chol_solve<T>(e.GU, e.kc, cntU, e.g, e.U, e.y, e.chw, 1, c,
+                             st);
     }
     }
     ProfScope pu(h, RGDBEK_PROF_COL_UPDATE);
@@ -827,7 +831,8 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
                             1, st);
     }
     if (!cg_r) {
-      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.r, e.J, e.w, 1, c, 1, 1, st);
+      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.r, e.J, e.w, e.chw, 1, c,
+                           st);
     } else {
       pcg_solve<T>(h, e.GJ, e.kr, cntJ, e.r, e.J, e.rho, e.w, e.cgr, maxs, itol, 1,
                    e.aat, e.m);
@@ -841,7 +846,7 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
       // projected equations recomputed from A^J itself
       launch_list_resid<T>(e.arm.a, e.arm.ld, e.n, e.J, cntJ, e.kr, e.b, e.z,
                            e.x, e.s, c, 1, st);
-      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.s, nullptr, e.w, 0, c, 1, 1,
+      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.s, nullptr, e.w, e.chw, 0, c,
                            st);
       launch_row_update<T>(e.arm.a, e.arm.ld, e.n, e.J, cntJ, e.kr, e.w, e.x,
                            e.upd, c, 1, st);
@@ -857,7 +862,8 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
                    e.aat, e.m);
     } else {
       launch_gram_gather<T>(e.aat, e.m, e.J, cntJ, e.kr, e.GJ, c, 1, st);
-      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.r, e.J, e.w, 1, c, 1, 1, st);
+      launch_chol_solve<T>(e.GJ, e.kr, cntJ, e.r, e.J, e.w, e.chw, 1, c,
+                           st);
     }
     }
     ProfScope pu(h, RGDBEK_PROF_ROW_UPDATE);
