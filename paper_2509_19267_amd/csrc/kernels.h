@@ -142,6 +142,10 @@ struct Csr {                 // CSR (or CSC viewed as CSR of the transpose)
   // Interleaved scratch of the many-right-hand-side products (rep >=
   // REP_MM_MIN): max(brows, bcols) * rep entries each, input and output.
   T *rep_in = nullptr, *rep_out = nullptr;
+  // Row groups of those products (rep.hip), when they pay: counts per mask,
+  // indices and values in group order (spans as ptr).
+  const int32_t *rg_cnt = nullptr, *rg_idx = nullptr;
+  const T *rg_val = nullptr;
   // Row ends when rows are not contiguous (the block copies of one stored
   // matrix keep A's row starts): row r spans [ptr[r], pend[r]).
   const int64_t *pend = nullptr;
@@ -501,6 +505,18 @@ constexpr int64_t REP_MM_MIN = 16;
 template <typename T>
 int launch_rep_mm(const Csr<T> &A, const T *in, T *out, double *part,
                   Ctrl *ctrl, int ph, int respect_done, hipStream_t st);
+// Row groups of the product: table entries for a matrix of brows rows, and
+// whether they pay (columns gathered by all groups against stored entries).
+// The build counts first (gidx null: cnt, and the columns into *total, which
+// starts at zero), then fills gidx and gval (nnz entries each, and
+// rep_rg_pad() zeros after them, which the product may read).
+int64_t rep_rg_table(int64_t brows);
+int64_t rep_rg_pad();
+bool rep_rg_pays(int64_t cols, int64_t nnz);
+template <typename T>
+void launch_rep_rg_build(const Csr<T> &A, int32_t *cnt,
+                         unsigned long long *total, int32_t *gidx, T *gval,
+                         hipStream_t st);
 // in[s * len + i] -> out[i * rep + s]
 template <typename T>
 void launch_rep_tin(const T *in, T *out, int64_t len, int64_t rep, Ctrl *ctrl,

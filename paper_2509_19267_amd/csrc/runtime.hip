@@ -57,6 +57,12 @@ struct MergePlan {
   int64_t nchunk = 0, ncross = 0;
 };
 
+// Row groups of the many-right-hand-side products of one CSR (see rep.hip).
+struct RowGroups {
+  int32_t *cnt = nullptr, *idx = nullptr;
+  bool pays = false;
+};
+
 struct Pool {
   std::vector<void *> ptrs;
   hipStream_t st = nullptr;   // zero-fills are ordered on this stream
@@ -145,6 +151,7 @@ struct rgdbek_ctx {
   int32_t *csr_longs = nullptr, *csc_longs = nullptr;
   int64_t csr_nlong = 0, csc_nlong = 0;
   MergePlan csr_mp, csc_mp;   // nonzero-balanced full-pass plans
+  RowGroups csr_rg, csc_rg;   // many right-hand sides: grouped rows
   double *rho = nullptr, *kappa = nullptr;
   Engine<double> e64;
   Engine<double> e64t;        // adjoint system (A^T), built on demand
@@ -382,6 +389,30 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       for (int i = 0; i < 3; ++i) rb[i] = P.alloc<T>(len, false);
       a.rep_in = at.rep_in = rb[0];
       a.rep_out = at.rep_out = rb[1];
+    }
+    // row groups of those products (more than 32 right-hand sides), where
+    // neighbouring rows share enough columns
+    if (h->rep > 32) {
+      auto groups = [&](Csr<T> &c, RowGroups &rg) {
+        if (!rg.cnt) {
+          rg.cnt = P.alloc<int32_t>(rep_rg_table(c.brows), false);
+          unsigned long long *tot = P.alloc<unsigned long long>(1), hv = 0;
+          launch_rep_rg_build<T>(c, rg.cnt, tot, nullptr, nullptr, h->st);
+          HIPCHK(hipMemcpyAsync(&hv, tot, sizeof(hv), hipMemcpyDeviceToHost,
+                                h->st));
+          HIPCHK(hipStreamSynchronize(h->st));
+          rg.pays = rep_rg_pays((int64_t)hv, h->nnz);
+          if (rg.pays) rg.idx = P.alloc<int32_t>(h->nnz + rep_rg_pad());
+        }
+        if (!rg.pays) return;
+        T *v = P.alloc<T>(h->nnz + rep_rg_pad());
+        launch_rep_rg_build<T>(c, rg.cnt, nullptr, rg.idx, v, h->st);
+        c.rg_cnt = rg.cnt;
+        c.rg_idx = rg.idx;
+        c.rg_val = v;
+      };
+      groups(a, transpose ? h->csc_rg : h->csr_rg);
+      groups(at, transpose ? h->csr_rg : h->csc_rg);
     }
     e.csr = a;
     e.csc = at;
