@@ -40,6 +40,8 @@ struct Ctrl {
   int64_t bl_first[2];    // block law: the weighted index (-1: none)
   // inner solver state (one per phase)
   double cg_rz[2], cg_rz0[2], cg_alpha[2], cg_beta[2];
+  double cg_rzp[2][2];    // cg_rz by phase and step parity (launches whose
+                          // blocks all read the old while one writes the new)
   int32_t cg_done[2], cg_steps[2];
   uint64_t sel_bar[2];    // grid-barrier arrivals of the persistent selection
   uint64_t sel_barbase[2];
@@ -134,16 +136,20 @@ __device__ __forceinline__ T ld_agent(const T *p) {
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// "Last block" election: every thread releases its prior global writes at
-// agent scope, thread 0 takes a ticket, and the block that takes the final
-// ticket acquires them and returns true (and re-arms the ticket).
+// "Last block" election for values exchanged through agent-scope stores and
+// loads (st_agent / ld_agent) alone: those stores go past the caches that
+// other blocks do not see, so that it is enough that every wave's have landed
+// (vmcnt) before thread 0 takes the block's ticket; no cache is written back
+// or invalidated (an agent-scope release per block cost about 12 us in a
+// launch of 512).  True in the block that takes the final ticket, which
+// re-arms it.
 __device__ __forceinline__ bool last_block(unsigned *ticket) {
   __shared__ int is_last;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned nb = gridDim.x * gridDim.y * gridDim.z;
-    unsigned t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL,
+    unsigned t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
     is_last = (t == nb - 1);
     if (is_last)
@@ -151,7 +157,6 @@ __device__ __forceinline__ bool last_block(unsigned *ticket) {
                          __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
-  if (is_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   return is_last != 0;
 }
 

@@ -370,6 +370,8 @@ struct SparseCg {
   // max(brows, bcols) * rep entries each
   T *t0 = nullptr, *t1 = nullptr, *t2 = nullptr;
 };
+// entries of SparseCg::part for products over len segments and blocks of cap
+int64_t sparse_cg_parts(int64_t len, int64_t cap);
 // Small sparse systems (both dimensions up to SPARSE_GRAM_MAX): dense
 // copies for the Gram matrices, and the block update out += sign A_L coef
 // (A_L the listed columns of A, as rows of the CSR view given).

@@ -495,10 +495,21 @@ constexpr unsigned SC_MAXB = 512;   // blocks of a launch that ends in a ticket
 constexpr unsigned SC_WIDE_MAXB = 512;   // blocks of the columns' wide product
 constexpr unsigned SC_WIDE_GRID_MIN = 8;  // slots per group above which the
                                           // wide product takes a full grid
+// Partials that every block of the next launch adds up for itself (a few
+// loads per thread) instead of a launch of its own.
+constexpr unsigned SC_SUM_MAX = 2048;
 // Larger blocks update the CG vectors with separate many-workgroup launches
 // (sc_cupd, sc_rupd1/2) instead of a walk by the last workgroup.
 constexpr int64_t SC_SERIAL_MAX = 16384;
 constexpr int SC_UNROLL = 8;        // loads in flight in one-block list walks
+
+// Sum of nb partials (stride st), the same in every thread and block.
+__device__ __forceinline__ double sum_parts(const double *__restrict__ part,
+                                            int nb, int st, double *sh) {
+  double t = 0.0;
+  for (int b = threadIdx.x; b < nb; b += SC_NT) t += part[(int64_t)b * st];
+  return block_sum<SC_NT>(t, sh);
+}
 
 template <typename T, int G>
 __global__ void __launch_bounds__(SC_NT)
@@ -589,8 +600,8 @@ sc_wide_col_grid(Csr<T> A, const T *__restrict__ phat, T *__restrict__ q,
 template <typename T>
 __global__ void __launch_bounds__(1024)
 sc_wide_col_fin(const double *__restrict__ part, int64_t nb,
-                const double *__restrict__ plong, int64_t nlong, Ctrl *ctrl,
-                int respect_done) {
+                const double *__restrict__ plong, int64_t nlong, int step,
+                Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (cg_done_at_start(ctrl, 0)) return;
   __shared__ double sh[1024 / WAVE];
@@ -600,7 +611,7 @@ sc_wide_col_fin(const double *__restrict__ part, int64_t nb,
   tot = block_sum<1024>(tot, sh);
   tot += block_sum<1024>(tl, sh);
   if (threadIdx.x == 0) {
-    const double gam = ctrl->cg_rz[0];
+    const double gam = step >= 0 ? ctrl->cg_rzp[0][step & 1] : ctrl->cg_rz[0];
     ctrl->cg_alpha[0] = tot > 0.0 ? gam / tot : 0.0;
     if (tot == 0.0) ctrl->cg_done[0] = 1;
   }
@@ -615,12 +626,23 @@ sc_narrow_col(Csr<T> At, const int32_t *__restrict__ U,
               T *__restrict__ z, int64_t m, T *__restrict__ sres,
               T *__restrict__ p, T *__restrict__ phat,
               double *__restrict__ part, const double *__restrict__ plong,
-              int64_t nlong, double tol, int par, int gridm,
-              const T *__restrict__ pre, Ctrl *ctrl, int respect_done) {
+              int64_t nlong, double tol, int par,
+              const T *__restrict__ pre, const double *__restrict__ qpart,
+              int nq, int step, Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (cg_done_at_start(ctrl, 0)) return;
   __shared__ double sh[SC_NT / WAVE];
-  const double alpha = ctrl->cg_alpha[0];
+  double alpha;
+  if (nq) {   // the wide product's partials of ||q||^2
+    const double qq = sum_parts(qpart, nq, 1, sh);
+    if (qq == 0.0) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->cg_done[0] = 1;
+      return;
+    }
+    alpha = ctrl->cg_rzp[0][step & 1] / qq;
+  } else {
+    alpha = ctrl->cg_alpha[0];
+  }
   const int64_t c = *cnt;
   // elementwise part: z -= alpha q on this block's slice of rows
   const int64_t per = (m + gridDim.x - 1) / gridDim.x;
@@ -652,12 +674,13 @@ sc_narrow_col(Csr<T> At, const int32_t *__restrict__ U,
     acc = group_sum<G>(acc);
     if (mine && lg == 0) {
       const T sv = sres[a] - (T)alpha * acc;
-      sres[a] = sv;
+      if (par) sres[a] = sv;
+      else st_agent(&sres[a], sv);   // read by the last block
       ss += (double)sv * (double)sv;
     }
   }
   ss = block_sum<SC_NT>(ss, sh);
-  if (gridm) {   // full grid: sc_narrow_col_fin reduces the partials
+  if (par) {   // the next launch reduces the partials
     if (threadIdx.x == 0) part[blockIdx.x] = ss;
     return;
   }
@@ -671,7 +694,7 @@ sc_narrow_col(Csr<T> At, const int32_t *__restrict__ U,
   const double gam = ctrl->cg_rz[0];
   const double beta = gam > 0.0 ? tot / gam : 0.0;
   // one block walks the whole list: keep SC_UNROLL loads in flight
-  for (int64_t k0 = threadIdx.x; !par && k0 < c; k0 += SC_UNROLL * SC_NT) {
+  for (int64_t k0 = threadIdx.x; k0 < c; k0 += SC_UNROLL * SC_NT) {
     T sv[SC_UNROLL], po[SC_UNROLL];
     int32_t ix[SC_UNROLL];
 #pragma unroll
@@ -703,7 +726,8 @@ sc_init(const int32_t *__restrict__ list, const int64_t *__restrict__ cnt,
         const T *__restrict__ rhs_src, const double *__restrict__ jac,
         T *__restrict__ sres, T *__restrict__ zz_or_null, T *__restrict__ p,
         T *__restrict__ phat, int32_t *__restrict__ pos,
-        double *__restrict__ part, Ctrl *ctrl, int ph, int respect_done) {
+        double *__restrict__ part, int gridm, Ctrl *ctrl, int ph,
+        int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   __shared__ double sh[SC_NT / WAVE];
   const int64_t c = *cnt;
@@ -731,6 +755,7 @@ sc_init(const int32_t *__restrict__ list, const int64_t *__restrict__ cnt,
     st_agent(&part[2 * blockIdx.x], rz);
     st_agent(&part[2 * blockIdx.x + 1], rr);
   }
+  if (gridm) return;   // sc_init_fin reduces the partials
   if (!last_block(&ctrl->ticket[6])) return;
   rz = 0.0;
   rr = 0.0;
@@ -745,6 +770,25 @@ sc_init(const int32_t *__restrict__ list, const int64_t *__restrict__ cnt,
     ctrl->cg_rz0[ph] = rr;
     ctrl->cg_alpha[ph] = 0.0;
     ctrl->cg_done[ph] = (rr == 0.0 || c == 0) ? 1 : 0;
+    ctrl->cg_steps[ph] = 0;
+  }
+}
+
+// Starts the CG of a phase from the partials of <res, zz> and ||res||^2.
+__global__ void __launch_bounds__(SC_NT)
+sc_init_fin(const double *__restrict__ part, int nb,
+            const int64_t *__restrict__ cnt, Ctrl *ctrl, int ph,
+            int respect_done) {
+  if (respect_done && ctrl_done(ctrl)) return;
+  __shared__ double sh[SC_NT / WAVE];
+  const double rz = sum_parts(part, nb, 2, sh);
+  const double rr = sum_parts(part + 1, nb, 2, sh);
+  if (threadIdx.x == 0) {
+    ctrl->cg_rz[ph] = rz;
+    ctrl->cg_rzp[ph][0] = rz;
+    ctrl->cg_rz0[ph] = rr;
+    ctrl->cg_alpha[ph] = 0.0;
+    ctrl->cg_done[ph] = (rr == 0.0 || *cnt == 0) ? 1 : 0;
     ctrl->cg_steps[ph] = 0;
   }
 }
@@ -771,7 +815,7 @@ sc_clear(const int32_t *__restrict__ list, const int64_t *__restrict__ cnt,
 __global__ void __launch_bounds__(1024)
 sc_narrow_col_fin(const double *__restrict__ part, int64_t nb,
                   const double *__restrict__ plong, int64_t nlong, double tol,
-                  Ctrl *ctrl, int respect_done) {
+                  int step, Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (cg_done_at_start(ctrl, 0)) return;
   __shared__ double sh[1024 / WAVE];
@@ -781,17 +825,17 @@ sc_narrow_col_fin(const double *__restrict__ part, int64_t nb,
   tot = block_sum<1024>(tot, sh);
   tot += block_sum<1024>(tl, sh);
   if (threadIdx.x == 0) {
-    const double gam = ctrl->cg_rz[0];
+    const double gam = ctrl->cg_rzp[0][step & 1];
     ctrl->cg_beta[0] = gam > 0.0 ? tot / gam : 0.0;
-    ctrl->cg_rz[0] = tot;
-    ctrl->cg_steps[0] += 1;
+    ctrl->cg_rzp[0][(step + 1) & 1] = tot;
+    ctrl->cg_steps[0] = step + 1;
     if (tot <= tol * tol * ctrl->cg_rz0[0]) ctrl->cg_done[0] = 1;
   }
 }
 __global__ void __launch_bounds__(1024)
 sc_narrow_row_fin(const double *__restrict__ part, int64_t nb,
-                  const double *__restrict__ plong, int64_t nlong, Ctrl *ctrl,
-                  int respect_done) {
+                  const double *__restrict__ plong, int64_t nlong, int step,
+                  Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (cg_done_at_start(ctrl, 1)) return;
   __shared__ double sh[1024 / WAVE];
@@ -801,24 +845,43 @@ sc_narrow_row_fin(const double *__restrict__ part, int64_t nb,
   tot = block_sum<1024>(tot, sh);
   tot += block_sum<1024>(tl, sh);
   if (threadIdx.x == 0) {
-    const double rz = ctrl->cg_rz[1];
+    const double rz = ctrl->cg_rzp[1][step & 1];
     ctrl->cg_alpha[1] = tot != 0.0 ? rz / tot : 0.0;
     ctrl->cg_steps[1] += 1;
     if (tot == 0.0) ctrl->cg_done[1] = 1;
   }
 }
 
-// Many-workgroup finish of a CG step for large blocks (SC_SERIAL_MAX).  Each
-// runs only when the narrow kernel of the same step completed (the step
-// counter equals step + 1), so steps after convergence stay no-ops.
+// Many-workgroup finish of a CG step for large blocks (SC_SERIAL_MAX).  The
+// step's scalars come from the product's partials, added up by every block
+// (nb of them; the block that keeps them is block 0), or, when those are too
+// many (nb == 0), from a launch in between; then each kernel runs only when
+// that launch completed the step (the step counter equals step + 1), so steps
+// after convergence stay no-ops.
+//   columns: gam' = ||s||^2, beta = gam'/gam, stop at gam' <= tol^2 gam_0
 template <typename T>
 __global__ void __launch_bounds__(SC_NT)
 sc_cupd(const int32_t *__restrict__ U, const int64_t *__restrict__ cnt,
         const T *__restrict__ sres, T *__restrict__ p, T *__restrict__ phat,
-        Ctrl *ctrl, int step, int respect_done) {
+        const double *__restrict__ part, int nb, double tol, Ctrl *ctrl,
+        int step, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
-  if (ctrl->cg_steps[0] != step + 1) return;
-  const double beta = ctrl->cg_beta[0];
+  double beta;
+  if (nb) {
+    if (cg_done_at_start(ctrl, 0)) return;
+    __shared__ double sh[SC_NT / WAVE];
+    const double tot = sum_parts(part, nb, 1, sh);
+    const double gam = ctrl->cg_rzp[0][step & 1];
+    beta = gam > 0.0 ? tot / gam : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ctrl->cg_rzp[0][(step + 1) & 1] = tot;
+      ctrl->cg_steps[0] = step + 1;
+      if (tot <= tol * tol * ctrl->cg_rz0[0]) ctrl->cg_done[0] = 1;
+    }
+  } else {
+    if (ctrl->cg_steps[0] != step + 1) return;
+    beta = ctrl->cg_beta[0];
+  }
   const int64_t c = *cnt;
   for (int64_t a = (int64_t)blockIdx.x * SC_NT + threadIdx.x; a < c;
        a += (int64_t)gridDim.x * SC_NT) {
@@ -828,19 +891,30 @@ sc_cupd(const int32_t *__restrict__ U, const int64_t *__restrict__ cnt,
   }
 }
 
-// rows: res -= alpha v, zz = res / rho, partials of <res, zz> and ||res||^2;
-// the last block forms beta and the stopping test
+// rows: alpha = rz / <p, v>; res -= alpha v, zz = res / rho, partials of
+// <res, zz> and ||res||^2
 template <typename T>
 __global__ void __launch_bounds__(SC_NT)
 sc_rupd1(const int32_t *__restrict__ J, const int64_t *__restrict__ cnt,
          const double *__restrict__ rho, T *__restrict__ res,
          T *__restrict__ zz, const T *__restrict__ v,
-         double *__restrict__ part, double tol, Ctrl *ctrl, int step,
-         int respect_done) {
+         const double *__restrict__ ppart, int nb, double *__restrict__ part,
+         Ctrl *ctrl, int step, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
-  if (ctrl->cg_steps[1] != step + 1) return;
   __shared__ double sh[SC_NT / WAVE];
-  const double alpha = ctrl->cg_alpha[1];
+  double alpha;
+  if (nb) {
+    if (cg_done_at_start(ctrl, 1)) return;
+    const double tot = sum_parts(ppart, nb, 1, sh);
+    alpha = tot != 0.0 ? ctrl->cg_rzp[1][step & 1] / tot : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ctrl->cg_alpha[1] = alpha;
+      ctrl->cg_steps[1] = step + 1;
+    }
+  } else {
+    if (ctrl->cg_steps[1] != step + 1) return;
+    alpha = ctrl->cg_alpha[1];
+  }
   const int64_t c = *cnt;
   double rz1 = 0.0, rr = 0.0;
   for (int64_t a = (int64_t)blockIdx.x * SC_NT + threadIdx.x; a < c;
@@ -856,34 +930,32 @@ sc_rupd1(const int32_t *__restrict__ J, const int64_t *__restrict__ cnt,
   rz1 = block_sum<SC_NT>(rz1, sh);
   rr = block_sum<SC_NT>(rr, sh);
   if (threadIdx.x == 0) {
-    st_agent(&part[2 * blockIdx.x], rz1);
-    st_agent(&part[2 * blockIdx.x + 1], rr);
-  }
-  if (!last_block(&ctrl->ticket[7])) return;
-  rz1 = 0.0;
-  rr = 0.0;
-  for (int b = threadIdx.x; b < (int)gridDim.x; b += SC_NT) {
-    rz1 += ld_agent(&part[2 * b]);
-    rr += ld_agent(&part[2 * b + 1]);
-  }
-  rz1 = block_sum<SC_NT>(rz1, sh);
-  rr = block_sum<SC_NT>(rr, sh);
-  if (threadIdx.x == 0) {
-    const double rz = ctrl->cg_rz[1];
-    ctrl->cg_beta[1] = rz != 0.0 ? rz1 / rz : 0.0;
-    ctrl->cg_rz[1] = rz1;
-    if (rr <= tol * tol * ctrl->cg_rz0[1]) ctrl->cg_done[1] = 1;
+    part[2 * blockIdx.x] = rz1;
+    part[2 * blockIdx.x + 1] = rr;
   }
 }
 
+// rows: beta = rz'/rz from sc_rupd1's nb partials, the stopping test, and
+// p = zz + beta p.  (Only block 0 raises the done flag, which no block of
+// this launch reads.)
 template <typename T>
 __global__ void __launch_bounds__(SC_NT)
 sc_rupd2(const int32_t *__restrict__ J, const int64_t *__restrict__ cnt,
          const T *__restrict__ zz, T *__restrict__ p, T *__restrict__ phat,
-         Ctrl *ctrl, int step, int respect_done) {
+         const double *__restrict__ part, int nb, double tol, Ctrl *ctrl,
+         int step, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (ctrl->cg_steps[1] != step + 1) return;
-  const double beta = ctrl->cg_beta[1];
+  __shared__ double sh[SC_NT / WAVE];
+  const double rz1 = sum_parts(part, nb, 2, sh);
+  const double rr = sum_parts(part + 1, nb, 2, sh);
+  const double rz = ctrl->cg_rzp[1][step & 1];
+  const double beta = rz != 0.0 ? rz1 / rz : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctrl->cg_rzp[1][(step + 1) & 1] = rz1;
+    if (rr <= tol * tol * ctrl->cg_rz0[1] || ctrl->cg_alpha[1] == 0.0)
+      ctrl->cg_done[1] = 1;
+  }
   const int64_t c = *cnt;
   for (int64_t a = (int64_t)blockIdx.x * SC_NT + threadIdx.x; a < c;
        a += (int64_t)gridDim.x * SC_NT) {
@@ -997,7 +1069,7 @@ sc_narrow_row(Csr<T> A, const int32_t *__restrict__ J,
               T *__restrict__ zz, T *__restrict__ p, T *__restrict__ v,
               T *__restrict__ phat, double *__restrict__ part,
               const double *__restrict__ plong, int64_t nlong, double tol,
-              int par, int gridm, const T *__restrict__ pre, Ctrl *ctrl,
+              int par, const T *__restrict__ pre, Ctrl *ctrl,
               int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   if (cg_done_at_start(ctrl, 1)) return;
@@ -1026,12 +1098,13 @@ sc_narrow_row(Csr<T> A, const int32_t *__restrict__ J,
     }
     acc = group_sum<G>(acc);
     if (mine && lg == 0) {
-      v[a] = acc;
+      if (par) v[a] = acc;
+      else st_agent(&v[a], acc);   // read by the last block
       pv += (double)acc * (double)p[a];
     }
   }
   pv = block_sum<SC_NT>(pv, sh);
-  if (gridm) {   // full grid: sc_narrow_row_fin reduces the partials
+  if (par) {   // the next launch reduces the partials
     if (threadIdx.x == 0) part[blockIdx.x] = pv;
     return;
   }
@@ -1044,14 +1117,6 @@ sc_narrow_row(Csr<T> A, const int32_t *__restrict__ J,
   tot += block_sum<SC_NT>(tl, sh);
   const double rz = ctrl->cg_rz[1];
   const double alpha = tot != 0.0 ? rz / tot : 0.0;
-  if (par) {   // sc_rupd1 and sc_rupd2 finish the step
-    if (threadIdx.x == 0) {
-      ctrl->cg_alpha[1] = alpha;
-      ctrl->cg_steps[1] += 1;
-      if (tot == 0.0) ctrl->cg_done[1] = 1;
-    }
-    return;
-  }
   double rz1 = 0.0, rr = 0.0;
   // one block walks the whole list: keep SC_UNROLL loads in flight
   for (int64_t k0 = threadIdx.x; k0 < c; k0 += SC_UNROLL * SC_NT) {
@@ -1115,10 +1180,30 @@ sc_row_finish(int64_t n, const T *__restrict__ u, T *__restrict__ x,
   if (j < n && alpha != 0.0) x[j] += (T)alpha * u[j];
 }
 
-static unsigned sc_init_blocks(int64_t cap) {
-  int64_t b = (cap + SC_NT - 1) / SC_NT;
-  if (b > 256) b = 256;
-  return (unsigned)(b < 1 ? 1 : b);
+// workgroups of the elementwise launches over a block
+static unsigned sc_list_blocks(int64_t cap) {
+  const int64_t b = (cap + SC_NT - 1) / SC_NT;
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, SC_SUM_MAX));
+}
+int64_t sparse_cg_parts(int64_t len, int64_t cap) {
+  return len / 4 + cap / 4 + 1024 + 4 * (int64_t)SC_SUM_MAX;
+}
+
+// Start of a phase's CG: for blocks finished in the last workgroup one
+// launch, else the partials and their sum apart.
+template <typename T>
+static void sc_start(const int32_t *list, const int64_t *cnt, int64_t cap,
+                     const T *rhs, const double *jac, T *zz, SparseCg<T> &w,
+                     int32_t *pos, int par, Ctrl *ctrl, int ph,
+                     int respect_done, hipStream_t st) {
+  const unsigned nb = sc_list_blocks(cap);
+  hipLaunchKernelGGL(sc_init<T>, dim3(nb), dim3(SC_NT), 0, st, list, cnt, rhs,
+                     jac, w.res, zz, w.p, w.phat, pos, w.part, par, ctrl, ph,
+                     respect_done);
+  if (par)
+    hipLaunchKernelGGL(sc_init_fin, dim3(1), dim3(SC_NT), 0, st,
+                       (const double *)w.part, (int)nb, cnt, ctrl, ph,
+                       respect_done);
 }
 
 template <typename T>
@@ -1147,29 +1232,32 @@ void launch_sparse_colproj(const Csr<T> &csr, const Csr<T> &csc,
   // for it); a replicated operator walks every segment with G lanes
   const int64_t nlw = csr.rep == 1 && w.pos ? csr.nlong : 0;
   const int64_t nln = csc.rep == 1 && w.pos ? csc.nlong : 0;
-  hipLaunchKernelGGL(sc_init<T>, dim3(sc_init_blocks(cap)), dim3(SC_NT), 0, st,
-                     U, count_dev, g, (const double *)nullptr, w.res,
-                     (T *)nullptr, w.p, w.phat, nln ? w.pos : (int32_t *)nullptr,
-                     w.part, ctrl, 0, respect_done);
+  // many right-hand sides: both products over interleaved vectors, and the
+  // listed product reads its value from them (one lane per listed column)
+  const bool mm = csr.rep >= REP_MM_MIN && w.t0 != nullptr;
+  const int par = (w.split || cap > SC_SERIAL_MAX || mm) ? 1 : 0;
+  sc_start<T>(U, count_dev, cap, g, (const double *)nullptr, (T *)nullptr, w,
+              nln ? w.pos : (int32_t *)nullptr, par, ctrl, 0, respect_done, st);
   const unsigned nbw = std::min<unsigned>(seg_blocks<T>(csr.rows, csr.group), SC_WIDE_MAXB);
   // many rows: a full grid and a separate reduction instead of a bounded
   // grid walking SC_WIDE_GRID_MIN or more row slots per thread group
   const unsigned nbg = seg_blocks<T>(csr.rows, csr.group);
-  const bool wide_grid = nbg >= SC_WIDE_GRID_MIN * SC_WIDE_MAXB &&
-                         (int64_t)nbg <= w.part_cap;
-  // many right-hand sides: both products over interleaved vectors, and the
-  // listed product reads its value from them (one lane per listed column)
-  const bool mm = csr.rep >= REP_MM_MIN && w.t0 != nullptr;
+  const bool wide_grid = par || (nbg >= SC_WIDE_GRID_MIN * SC_WIDE_MAXB &&
+                                 (int64_t)nbg <= w.part_cap);
   const int gn = mm ? 1 : csc.group;
-  unsigned nbn = std::min<unsigned>(seg_blocks<T>(cap, gn), SC_MAXB);
-  if (nbn < 64) nbn = 64;
-  const int par = (w.split || cap > SC_SERIAL_MAX) ? 1 : 0;
-  // large blocks: the listed product over a full grid, reduced by a
-  // separate launch (no grid-stride walk, no last-workgroup ticket)
-  const unsigned nbnf = seg_blocks<T>(cap, gn);
-  const bool narrow_grid = par && nbnf > SC_MAXB && (int64_t)nbnf <= w.part_cap;
-  const unsigned nbu = std::min<unsigned>(
-      (unsigned)((cap + SC_NT - 1) / SC_NT), SC_MAXB);
+  // large blocks: the listed product over a full grid (no grid-stride walk,
+  // no last-workgroup ticket)
+  const unsigned nbn = par ? seg_blocks<T>(cap, gn)
+                           : std::max(64u, std::min(seg_blocks<T>(cap, gn),
+                                                    SC_MAXB));
+  const unsigned nbu = sc_list_blocks(cap);
+  // The step's scalars: added up from the partials by the next launch where
+  // those are few, else by a launch in between (which also adds the long
+  // segments').  Where the listed product
+  // reads the wide one's partials, its own lie apart.
+  const bool sum_n = par && !nln && nbn <= SC_SUM_MAX;
+  const bool sum_w = sum_n && !mm && !nlw && nbg <= SC_SUM_MAX;
+  double *pn = sum_n ? w.part + (w.part_cap - 4 * (int64_t)SC_SUM_MAX) : w.part;
   for (int s = 0; s < max_steps; ++s) {
     if (mm) {
       // q = A phat for every right-hand side, ||q||^2 -> alpha; then A^T q
@@ -1179,7 +1267,7 @@ void launch_sparse_colproj(const Csr<T> &csr, const Csr<T> &csc,
                                        respect_done, st);
       hipLaunchKernelGGL(sc_wide_col_fin<T>, dim3(1), dim3(1024), 0, st,
                          (const double *)w.part, (int64_t)nbm,
-                         (const double *)nullptr, (int64_t)0, ctrl,
+                         (const double *)nullptr, (int64_t)0, s, ctrl,
                          respect_done);
       launch_rep_tout<T>(w.t1, w.wide, (T *)nullptr, csr.brows, csr.rep, ctrl,
                          0, respect_done, st);
@@ -1195,9 +1283,11 @@ void launch_sparse_colproj(const Csr<T> &csr, const Csr<T> &csc,
                   hipLaunchKernelGGL((sc_wide_col_grid<T, GG>), dim3(nbg),
                                      dim3(SC_NT), 0, st, csr, w.phat, w.wide,
                                      w.part, nlw, ctrl, respect_done));
-      hipLaunchKernelGGL(sc_wide_col_fin<T>, dim3(1), dim3(1024), 0, st,
-                         (const double *)w.part, (int64_t)nbg,
-                         (const double *)w.plong, nlw, ctrl, respect_done);
+      if (!sum_w)
+        hipLaunchKernelGGL(sc_wide_col_fin<T>, dim3(1), dim3(1024), 0, st,
+                           (const double *)w.part, (int64_t)nbg,
+                           (const double *)w.plong, nlw, par ? s : -1, ctrl,
+                           respect_done);
     } else {
       RG_SWITCH_G(csr.group, hipLaunchKernelGGL((sc_wide_col<T, GG>), dim3(nbw),
                                                 dim3(SC_NT), 0, st, csr, w.phat,
@@ -1210,24 +1300,25 @@ void launch_sparse_colproj(const Csr<T> &csr, const Csr<T> &csc,
                          0, st, csc, w.pos, w.wide, w.res, w.p, w.plong, ctrl,
                          0, respect_done);
     RG_SWITCH_G(gn,
-                hipLaunchKernelGGL((sc_narrow_col<T, GG>),
-                                   dim3(narrow_grid ? nbnf : nbn),
+                hipLaunchKernelGGL((sc_narrow_col<T, GG>), dim3(nbn),
                                    dim3(SC_NT), 0, st, csc, U, count_dev,
                                    w.wide, z, csr.rows, w.res, w.p, w.phat,
-                                   w.part, w.plong, nln, tol, par,
-                                   narrow_grid ? 1 : 0,
+                                   pn, w.plong, nln, tol, par,
                                    mm ? (const T *)w.t2 : (const T *)nullptr,
-                                   ctrl, respect_done));
-    if (narrow_grid)
+                                   (const double *)w.part,
+                                   sum_w ? (int)nbg : 0, s, ctrl,
+                                   respect_done));
+    if (par && !sum_n)
       hipLaunchKernelGGL(sc_narrow_col_fin, dim3(1), dim3(1024), 0, st,
-                         (const double *)w.part, (int64_t)nbnf,
-                         (const double *)w.plong, nln, tol, ctrl,
+                         (const double *)pn, (int64_t)nbn,
+                         (const double *)w.plong, nln, tol, s, ctrl,
                          respect_done);
     if (par)
       hipLaunchKernelGGL(sc_cupd<T>, dim3(nbu), dim3(SC_NT), 0, st, U,
-                         count_dev, w.res, w.p, w.phat, ctrl, s, respect_done);
+                         count_dev, w.res, w.p, w.phat, (const double *)pn,
+                         sum_n ? (int)nbn : 0, tol, ctrl, s, respect_done);
   }
-  hipLaunchKernelGGL(sc_clear<T>, dim3(64), dim3(SC_NT), 0, st, U, count_dev,
+  hipLaunchKernelGGL(sc_clear<T>, dim3(nbu), dim3(SC_NT), 0, st, U, count_dev,
                      cap, w.phat, nln ? w.pos : (int32_t *)nullptr, ctrl,
                      respect_done);
 }
@@ -1240,20 +1331,20 @@ void launch_sparse_rowproj(const Csr<T> &csr, const Csr<T> &csc,
                            Ctrl *ctrl, int respect_done, hipStream_t st) {
   const int64_t nlw = csc.rep == 1 && w.pos ? csc.nlong : 0;
   const int64_t nln = csr.rep == 1 && w.pos ? csr.nlong : 0;
-  hipLaunchKernelGGL(sc_init<T>, dim3(sc_init_blocks(cap)), dim3(SC_NT), 0, st,
-                     J, count_dev, r, rho, w.res, w.v, w.p, w.phat,
-                     nln ? w.pos : (int32_t *)nullptr, w.part, ctrl, 1,
-                     respect_done);
-  // w.v doubles as the Jacobi-scaled residual buffer zz during steps
   const unsigned nbw = seg_blocks<T>(csc.rows, csc.group);
   const bool mm = csr.rep >= REP_MM_MIN && w.t0 != nullptr;
   const int gn = mm ? 1 : csr.group;
-  const unsigned nbn = std::min<unsigned>(seg_blocks<T>(cap, gn), SC_MAXB);
-  const int par = (w.split || cap > SC_SERIAL_MAX) ? 1 : 0;
-  const unsigned nbnf = seg_blocks<T>(cap, gn);
-  const bool narrow_grid = par && nbnf > SC_MAXB && (int64_t)nbnf <= w.part_cap;
-  const unsigned nbu = std::min<unsigned>(
-      (unsigned)((cap + SC_NT - 1) / SC_NT), SC_MAXB);
+  const int par = (w.split || cap > SC_SERIAL_MAX || mm) ? 1 : 0;
+  // w.v doubles as the Jacobi-scaled residual buffer zz during steps
+  sc_start<T>(J, count_dev, cap, r, rho, w.v, w,
+              nln ? w.pos : (int32_t *)nullptr, par, ctrl, 1, respect_done, st);
+  const unsigned nbn = par ? seg_blocks<T>(cap, gn)
+                           : std::min<unsigned>(seg_blocks<T>(cap, gn), SC_MAXB);
+  const unsigned nbu = sc_list_blocks(cap);
+  // as for the columns: the product's partials added up by sc_rupd1 where
+  // they are few; sc_rupd1's own lie apart
+  const bool sum_n = par && !nln && nbn <= SC_SUM_MAX;
+  double *pu = w.part + (w.part_cap - 4 * (int64_t)SC_SUM_MAX);
   for (int s = 0; s < max_steps; ++s) {
     if (mm) {
       // u = A^T phat for every right-hand side (the pending x += alpha u
@@ -1281,30 +1372,32 @@ void launch_sparse_rowproj(const Csr<T> &csr, const Csr<T> &csc,
                          0, st, csr, w.pos, w.wide, w.v + cap, w.p, w.plong,
                          ctrl, 1, respect_done);
     RG_SWITCH_G(gn,
-                hipLaunchKernelGGL((sc_narrow_row<T, GG>),
-                                   dim3(narrow_grid ? nbnf : nbn),
+                hipLaunchKernelGGL((sc_narrow_row<T, GG>), dim3(nbn),
                                    dim3(SC_NT), 0, st, csr, J, count_dev,
                                    w.wide, rho, w.res, w.v, w.p,
                                    w.v + cap, w.phat, w.part, w.plong, nln,
-                                   tol, par, narrow_grid ? 1 : 0,
+                                   tol, par,
                                    mm ? (const T *)w.t2 : (const T *)nullptr,
                                    ctrl, respect_done));
-    if (narrow_grid)
-      hipLaunchKernelGGL(sc_narrow_row_fin, dim3(1), dim3(1024), 0, st,
-                         (const double *)w.part, (int64_t)nbnf,
-                         (const double *)w.plong, nln, ctrl, respect_done);
     if (par) {
+      if (!sum_n)
+        hipLaunchKernelGGL(sc_narrow_row_fin, dim3(1), dim3(1024), 0, st,
+                           (const double *)w.part, (int64_t)nbn,
+                           (const double *)w.plong, nln, s, ctrl,
+                           respect_done);
       hipLaunchKernelGGL(sc_rupd1<T>, dim3(nbu), dim3(SC_NT), 0, st, J,
-                         count_dev, rho, w.res, w.v, w.v + cap, w.part, tol,
+                         count_dev, rho, w.res, w.v, w.v + cap,
+                         (const double *)w.part, sum_n ? (int)nbn : 0, pu,
                          ctrl, s, respect_done);
       hipLaunchKernelGGL(sc_rupd2<T>, dim3(nbu), dim3(SC_NT), 0, st, J,
-                         count_dev, w.v, w.p, w.phat, ctrl, s, respect_done);
+                         count_dev, w.v, w.p, w.phat, (const double *)pu,
+                         (int)nbu, tol, ctrl, s, respect_done);
     }
   }
   hipLaunchKernelGGL(sc_row_finish<T>, dim3((unsigned)((csc.rows + SC_NT - 1) / SC_NT)),
                      dim3(SC_NT), 0, st, csc.rows, w.wide, x, ctrl,
                      respect_done);
-  hipLaunchKernelGGL(sc_clear<T>, dim3(64), dim3(SC_NT), 0, st, J, count_dev,
+  hipLaunchKernelGGL(sc_clear<T>, dim3(nbu), dim3(SC_NT), 0, st, J, count_dev,
                      cap, w.phat, nln ? w.pos : (int32_t *)nullptr, ctrl,
                      respect_done);
 }

@@ -424,7 +424,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       sc.p = P.alloc<T>(cap);
       sc.res = P.alloc<T>(cap);
       sc.v = P.alloc<T>(2 * cap);
-      const int64_t nb = std::max(e.m, e.n) / 4 + cap / 4 + 1024;
+      const int64_t nb = sparse_cg_parts(std::max(e.m, e.n), cap);
       sc.part = P.alloc<double>(nb);
       sc.part_cap = nb;
       sc.split = (h->p.flags & RGDBEK_FLAG_CG_SPLIT) ? 1 : 0;
