@@ -175,20 +175,21 @@ __device__ __forceinline__ bool cg_done_at_start(const Ctrl *c, int ph) {
 
 // Grid barrier of a persistent launch (every workgroup resident): arrivals
 // are counted in a 64-bit counter that only grows; barrier number b of a
-// launch completes when the counter reaches base + b * gridDim.x.  Thread 0
-// releases the workgroup's writes at agent scope, arrives, polls, and
-// acquires.  Polls are bounded (GRID_SPIN_MAX, seconds): a timed-out wait
-// sets *fail, which also ends the waits of the other workgroups, so the
-// launch always drains.
+// launch completes when the counter reaches base + b * gridDim.x.  It orders
+// values exchanged through agent-scope accesses (st_agent, ld_agent, device
+// atomics) alone: every wave waits until its own have landed, then thread 0
+// arrives and polls; no cache is written back or invalidated.  Polls are
+// bounded (GRID_SPIN_MAX, seconds): a timed-out wait sets *fail, which also
+// ends the waits of the other workgroups, so the launch always drains.
 constexpr int64_t GRID_SPIN_MAX = 1ll << 22;
 // Arrive at barrier number `target` (counter value after every workgroup
 // arrived); returns false after a timed-out wait.
 __device__ __forceinline__ bool grid_barrier(uint64_t *ctr, uint64_t target,
                                              int32_t *fail) {
   __shared__ int s_ok;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __hip_atomic_fetch_add(ctr, (uint64_t)1, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     int64_t spins = 0;
@@ -196,10 +197,13 @@ __device__ __forceinline__ bool grid_barrier(uint64_t *ctr, uint64_t target,
     while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
            target) {
       __builtin_amdgcn_s_sleep(1);
-      if (++spins > GRID_SPIN_MAX || ld_agent(fail) != 0) { ok = 0; break; }
+      if (++spins > GRID_SPIN_MAX ||
+          ((spins & 63) == 0 && ld_agent(fail) != 0)) {
+        ok = 0;
+        break;
+      }
     }
     if (!ok) st_agent(fail, 1);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     s_ok = ok;
   }
   __syncthreads();

@@ -1621,6 +1621,26 @@ noalloc_zero_kernel(uint4 *p, int64_t n16) {
 }
 
 namespace {
+// Work space of one draw in one allocation, laid out as the static array is
+// and cleared the same way (one allocation and one launch cost a small draw
+// less than one of each per array).
+Ctrl *draw_scratch(Pool &P, int64_t d, SelectScratch &sc) {
+  const size_t keys = na_align(
+      NA_BLK + (size_t)(select_scratch_blocks(d) + 64) * sizeof(int32_t));
+  unsigned char *base = P.alloc<unsigned char>(
+      (int64_t)(keys + (size_t)(d + 64) * sizeof(uint64_t)), false);
+  hipLaunchKernelGGL(noalloc_zero_kernel, dim3(64), dim3(256), 0, P.st,
+                     (uint4 *)base, (int64_t)(keys / sizeof(uint4)));
+  sc.pers = (SelPersist *)(base + NA_PERS);
+  sc.ncu = device_cus();
+  sc.keys = (uint64_t *)(base + keys);
+  sc.hist = (unsigned *)(base + NA_HIST);
+  sc.ckey = (uint64_t *)(base + NA_CKEY);
+  sc.cidx = (int64_t *)(base + NA_CIDX);
+  sc.blk = (int32_t *)(base + NA_BLK);
+  return (Ctrl *)(base + NA_CTRL);
+}
+
 // Device address of `scratch` on the current device, looked up once per
 // device: the host-side name is only a stand-in for the symbol.
 unsigned char *noalloc_scratch_ptr() {
@@ -2106,14 +2126,7 @@ rgdbek_status rgdbek_select(const double *eps, int64_t d, int64_t k,
   P.st = st;
   rgdbek_status s = guarded(nullptr, [&]() {
     SelectScratch sc;
-    sc.pers = P.alloc<SelPersist>(1);
-    sc.ncu = device_cus();
-    sc.keys = P.alloc<uint64_t>(d + 64, false);
-    sc.hist = P.alloc<unsigned>(2048);
-    sc.ckey = P.alloc<uint64_t>(4096);
-    sc.cidx = P.alloc<int64_t>(4096);
-    sc.blk = P.alloc<int32_t>(select_scratch_blocks(d) + 64);
-    Ctrl *c = P.alloc<Ctrl>(1);
+    Ctrl *c = draw_scratch(P, d, sc);
     launch_fill_ctrl_it(c, (int64_t)it, st);
     launch_select<double>(eps, d, k, floor, seed, key1, phase, sys, 0, sc,
                           out_idx, c, 0, st);
@@ -2148,16 +2161,9 @@ rgdbek_status rgdbek_select_block_law(const double *eps, int64_t d, int64_t s,
   P.st = st;
   rgdbek_status r = guarded(nullptr, [&]() {
     SelectScratch sc;
-    sc.pers = P.alloc<SelPersist>(1);
-    sc.ncu = device_cus();
-    sc.keys = P.alloc<uint64_t>(d + 64, false);
-    sc.hist = P.alloc<unsigned>(2048);
-    sc.ckey = P.alloc<uint64_t>(4096);
-    sc.cidx = P.alloc<int64_t>(4096);
-    sc.blk = P.alloc<int32_t>(select_scratch_blocks(d) + 64);
+    Ctrl *c = draw_scratch(P, d, sc);
     double *w = P.alloc<double>(d + 64);
     int32_t *tmp = P.alloc<int32_t>(s + 64);
-    Ctrl *c = P.alloc<Ctrl>(1);
     launch_fill_ctrl_it(c, (int64_t)it, st);
     launch_select_block_law<double>(eps, d, s, floor, seed, key1, phase, sys, 0,
                                     sc, w, tmp, out_idx, c, 0, st);

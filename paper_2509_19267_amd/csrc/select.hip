@@ -150,16 +150,16 @@ constexpr int WG_CAND = 256;
 constexpr int WG_UNROLL = 8;
 constexpr int WG_LDS_KEYS = 8192;
 
-__device__ __forceinline__ int wg_shift(int lev) { return lev < 5 ? 53 - 11 * lev : 0; }
-__device__ __forceinline__ int wg_width(int lev) { return lev < 5 ? 11 : 9; }
-
-// exclusive prefix of v over the workgroup (thread order); *tot = sum
-__device__ __forceinline__ int64_t wg_scan(int64_t v, int64_t *sh, int64_t *tot) {
+// Exclusive prefix of v over a workgroup of NT threads (thread order);
+// *tot = sum.  Counts below 2^31: the waves scan 32 bits.
+template <int NT>
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t *sh,
+                                              int64_t *tot) {
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  int64_t inc = v;
+  int inc = (int)v;
 #pragma unroll
   for (int o = 1; o < WAVE; o <<= 1) {
-    const int64_t u = __shfl_up(inc, o, WAVE);
+    const int u = __shfl_up(inc, o, WAVE);
     if (lane >= o) inc += u;
   }
   __syncthreads();
@@ -167,12 +167,46 @@ __device__ __forceinline__ int64_t wg_scan(int64_t v, int64_t *sh, int64_t *tot)
   __syncthreads();
   int64_t before = 0, all = 0;
 #pragma unroll
-  for (int i = 0; i < WG_NT / WAVE; ++i) {
+  for (int i = 0; i < NT / WAVE; ++i) {
     if (i < wv) before += sh[i];
     all += sh[i];
   }
   *tot = all;
   return before + inc - v;
+}
+
+// The bin that holds rank krem (from 1) of a histogram of nb <= PER * NT
+// bins, thread t holding bins PER t .. in v: its number, the count before it
+// and its own, by the thread that finds it.
+template <int NT, int PER>
+__device__ __forceinline__ void find_bin(const unsigned (&v)[PER], int64_t krem,
+                                         int64_t *sh, int64_t *bin,
+                                         int64_t *before, int64_t *count) {
+  int64_t ls = 0, tot;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) ls += v[i];
+  int64_t acc = block_scan<NT>(ls, sh, &tot);
+  if (acc < krem && krem <= acc + ls) {
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (!found && acc + (int64_t)v[i] >= krem) {
+        *bin = (int64_t)threadIdx.x * PER + i;
+        *before = acc;
+        *count = v[i];
+        found = true;
+      }
+      acc += v[i];
+    }
+  }
+}
+
+__device__ __forceinline__ int wg_shift(int lev) { return lev < 5 ? 53 - 11 * lev : 0; }
+__device__ __forceinline__ int wg_width(int lev) { return lev < 5 ? 11 : 9; }
+
+// exclusive prefix of v over the workgroup (thread order); *tot = sum
+__device__ __forceinline__ int64_t wg_scan(int64_t v, int64_t *sh, int64_t *tot) {
+  return block_scan<WG_NT>(v, sh, tot);
 }
 
 // From keys (d of them, SENT for zero weights), the count of positive keys
@@ -200,28 +234,14 @@ __device__ __forceinline__ int64_t resolve_compact(const uint64_t *__restrict__ 
     while (true) {
       const int sh = wg_shift(lev), wd = wg_width(lev);
       const int nb = 1 << wd;
-      if (wv == 0) {
-        const int per = nb / WAVE;
-        int64_t ls = 0;
-        for (int i = 0; i < per; ++i) ls += hist[lane * per + i];
-        int64_t inc = ls;
+      {
+        unsigned v[2048 / NT];
 #pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) {
-          const int64_t u = __shfl_up(inc, o, WAVE);
-          if (lane >= o) inc += u;
+        for (int i = 0; i < 2048 / NT; ++i) {
+          const int b = tid * (2048 / NT) + i;
+          v[i] = b < nb ? hist[b] : 0u;
         }
-        const int64_t exc = inc - ls;
-        if (exc < krem && krem <= inc) {
-          int64_t acc = exc;
-          int b = lane * per;
-          for (;; ++b) {
-            if (acc + (int64_t)hist[b] >= krem) break;
-            acc += hist[b];
-          }
-          s_b = b;
-          s_acc = acc;
-          s_cb = hist[b];
-        }
+        find_bin<NT>(v, krem, sh64, &s_b, &s_acc, &s_cb);
       }
       if (tid == 0) s_nc = 0u;
       __syncthreads();
@@ -907,24 +927,7 @@ __device__ __forceinline__ int sp_width(int lev) { return lev < 5 ? 11 : 9; }
 
 // exclusive prefix of v over the workgroup (thread order); *tot = sum
 __device__ __forceinline__ int64_t sp_scan(int64_t v, int64_t *sh, int64_t *tot) {
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  int64_t inc = v;
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const int64_t u = __shfl_up(inc, o, WAVE);
-    if (lane >= o) inc += u;
-  }
-  __syncthreads();
-  if (lane == WAVE - 1) sh[wv] = inc;
-  __syncthreads();
-  int64_t before = 0, all = 0;
-#pragma unroll
-  for (int i = 0; i < SP_NT / WAVE; ++i) {
-    if (i < wv) before += sh[i];
-    all += sh[i];
-  }
-  *tot = all;
-  return before + inc - v;
+  return block_scan<SP_NT>(v, sh, tot);
 }
 
 template <typename T, int KPT>
@@ -954,8 +957,12 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
 
   if (blockIdx.x == 0) {
     unsigned *gh = &sp->gh[0][0];
-    for (int i = tid; i < 6 * 2048; i += SP_NT) gh[i] = 0u;
-    if (tid == 0) { sp->gpos = 0ull; sp->ncand = 0ull; sp->tidx = -1; }
+    for (int i = tid; i < 6 * 2048; i += SP_NT) st_agent(&gh[i], 0u);
+    if (tid == 0) {
+      st_agent(&sp->gpos, 0ull);
+      st_agent(&sp->ncand, 0ull);
+      st_agent(&sp->tidx, (int64_t)-1);
+    }
   }
   // 1. largest finite weight
   double mx = 0.0;
@@ -974,7 +981,7 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
   __syncthreads();
   if (tid == 0) {
     for (int i = 0; i < SP_NT / WAVE; ++i) mx = shd[i] > mx ? shd[i] : mx;
-    sp->gmax[blockIdx.x] = mx;
+    st_agent(&sp->gmax[blockIdx.x], mx);
   }
   if (!grid_barrier(bar, bbase + (++nbar) * P, fail)) return;
   double gm = 0.0;
@@ -1037,31 +1044,14 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
     while (true) {
       const int sh = sp_shift(lev), wd = sp_width(lev);
       const int nb = 1 << wd;
-      for (int i = tid; i < nb; i += SP_NT) hist[i] = ld_agent(&sp->gh[lev][i]);
-      __syncthreads();
-      if (wv == 0) {
-        // bucket holding rank krem: lane sums of nb/64 bins, wave scan
-        const int per = nb / WAVE;
-        int64_t ls = 0;
-        for (int i = 0; i < per; ++i) ls += hist[lane * per + i];
-        int64_t inc = ls;
+      {
+        unsigned v[2048 / SP_NT];
 #pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) {
-          const int64_t u = __shfl_up(inc, o, WAVE);
-          if (lane >= o) inc += u;
+        for (int i = 0; i < 2048 / SP_NT; ++i) {
+          const int b = tid * (2048 / SP_NT) + i;
+          v[i] = b < nb ? ld_agent(&sp->gh[lev][b]) : 0u;
         }
-        const int64_t exc = inc - ls;
-        if (exc < krem && krem <= inc) {
-          int64_t acc = exc;
-          int b = lane * per;
-          for (;; ++b) {
-            if (acc + (int64_t)hist[b] >= krem) break;
-            acc += hist[b];
-          }
-          s_b = b;
-          s_acc = acc;
-          s_cb = hist[b];
-        }
+        find_bin<SP_NT>(v, krem, sh64, &s_b, &s_acc, &s_cb);
       }
       __syncthreads();
       prefix = (prefix << wd) | (uint64_t)s_b;
@@ -1093,8 +1083,9 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
             const uint64_t kk = key[4 * i + q];
             if (kk != SENT && (kk >> sh) == prefix) {
               if (slot < SP_CAND) {
-                sp->ckey[slot] = kk;
-                sp->cidx[slot] = base + 4 * ((int64_t)i * SP_NT + tid) + q;
+                st_agent(&sp->ckey[slot], kk);
+                st_agent(&sp->cidx[slot],
+                         base + 4 * ((int64_t)i * SP_NT + tid) + q);
               }
               ++slot;
             }
@@ -1129,7 +1120,7 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
 #pragma unroll
         for (int i = 0; i < KPT; ++i) mine += key[i] == tkey;
         mine = block_sum_i64<SP_NT>(mine, sh64);
-        if (tid == 0) sp->cnt[blockIdx.x] = mine;
+        if (tid == 0) st_agent(&sp->cnt[blockIdx.x], mine);
         if (!grid_barrier(bar, bbase + (++nbar) * P, fail)) return;
         int64_t before = 0;
         for (int b = tid; b < (int)blockIdx.x; b += SP_NT) before += ld_agent(&sp->cnt[b]);
@@ -1185,7 +1176,7 @@ sel_persist_kernel(const T *__restrict__ eps, int64_t d, int64_t k,
       mine += take(key[4 * i + q], base + 4 * ((int64_t)i * SP_NT + tid) + q,
                    lo, tkey, tidx);
   mine = block_sum_i64<SP_NT>(mine, sh64);
-  if (tid == 0) sp->cnt[blockIdx.x] = mine;
+  if (tid == 0) st_agent(&sp->cnt[blockIdx.x], mine);
   if (!grid_barrier(bar, bbase + (++nbar) * P, fail)) return;
   int64_t before = 0, total = 0;
   for (int b = tid; b < P; b += SP_NT) {
