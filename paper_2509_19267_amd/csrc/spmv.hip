@@ -123,6 +123,7 @@ segdot_long(Csr<T> A, SegArgs<T> a, int64_t part_base, Ctrl *ctrl,
 constexpr int MP_NT = 256;
 constexpr int MP_K = (int)(MP_CH / WAVE);
 constexpr int MP_WPB = MP_NT / WAVE;
+constexpr int MP_SUM = 8;              // LDS reads in flight per row
 
 template <typename T>
 __device__ __forceinline__ void mp_finish(int epi, const SegArgs<T> &a,
@@ -135,8 +136,9 @@ template <typename T, int EPI>
 __global__ void __launch_bounds__(MP_NT)
 mp_chunks(Csr<T> A, SegArgs<T> a, Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
-  __shared__ T sp[MP_WPB][MP_CH];
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  __shared__ T sp[MP_WPB][MP_CH + MP_SUM];
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int64_t c = (int64_t)blockIdx.x * MP_WPB + wv;
   double pb = 0.0, pr = 0.0;
   if (c < A.mp_nchunk) {
@@ -144,16 +146,34 @@ mp_chunks(Csr<T> A, SegArgs<T> a, Ctrl *ctrl, int respect_done) {
     const int64_t eh = A.nnz < e0 + MP_CH ? A.nnz : e0 + MP_CH;   // data end
     // products of this lane's MP_K consecutive nonzeros
     const int64_t eb = e0 + (int64_t)lane * MP_K;
+    const int64_t rs = A.mp_rs[c], re = A.mp_rs[c + 1];
+    // the lane's first owned row, loaded beside the gathers
+    const int64_t rf = rs + lane < re ? rs + lane : rs;
+    int64_t f0, f1, pe = 0;
     T pv[MP_K];
     if (eh == e0 + MP_CH) {
-      // full chunk: one 16-byte index load and MP_K*sizeof(T) value bytes
-      typedef int32_t i4 __attribute__((ext_vector_type(MP_K)));
-      typedef T tv __attribute__((ext_vector_type(MP_K)));
-      const i4 ix = *reinterpret_cast<const i4 *>(A.idx + eb);
-      const tv vv = *reinterpret_cast<const tv *>(A.val + eb);
+      // full chunk: 16-byte loads of the indices and values, not kept in
+      // the caches that the gathered vector needs
+      typedef int32_t i4 __attribute__((ext_vector_type(4)));
+      typedef T tv __attribute__((ext_vector_type(4)));
+      i4 ix[MP_K / 4];
+      tv vv[MP_K / 4];
 #pragma unroll
-      for (int j = 0; j < MP_K; ++j) pv[j] = vv[j] * a.v[ix[j]];
+      for (int u = 0; u < MP_K / 4; ++u) {
+        ix[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const i4 *>(A.idx + eb) + u);
+        vv[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const tv *>(A.val + eb) + u);
+      }
+      f0 = A.ptr[rf];
+      f1 = A.ptr[rf + 1];
+      if (c > 0 && rs > 0) pe = A.ptr[rs];
+#pragma unroll
+      for (int j = 0; j < MP_K; ++j) pv[j] = vv[j / 4][j % 4] * a.v[ix[j / 4][j % 4]];
     } else {
+      f0 = A.ptr[rf];
+      f1 = A.ptr[rf + 1];
+      if (c > 0 && rs > 0) pe = A.ptr[rs];
 #pragma unroll
       for (int j = 0; j < MP_K; ++j) {
         const int64_t e = eb + j;
@@ -164,11 +184,9 @@ mp_chunks(Csr<T> A, SegArgs<T> a, Ctrl *ctrl, int respect_done) {
 #pragma unroll
     for (int j = 0; j < MP_K; ++j) sp[wv][lane * MP_K + j] = pv[j];
     // lead partial: the row that began before e0 and continues here
-    const int64_t rs = A.mp_rs[c], re = A.mp_rs[c + 1];
     T lead = (T)0;
     if (c > 0 && rs > 0) {
-      const int64_t pe = A.ptr[rs] - e0;     // where the entering row stops
-      const int64_t lim = pe < MP_CH ? pe : MP_CH;
+      const int64_t lim = pe - e0 < MP_CH ? pe - e0 : MP_CH;   // where it stops
 #pragma unroll
       for (int j = 0; j < MP_K; ++j)
         if (lane * MP_K + j < lim) lead += pv[j];
@@ -179,12 +197,22 @@ mp_chunks(Csr<T> A, SegArgs<T> a, Ctrl *ctrl, int respect_done) {
     // stores before the loads (one wave, so a wave-scope fence suffices)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    // owned rows: lane-strided, each summed in element order from LDS
+    // owned rows: lane-strided, each summed in element order from LDS,
+    // MP_SUM reads in flight (a lane's long row would hold up the wave for
+    // one LDS latency per element)
     for (int64_t r = rs + lane; r < re; r += WAVE) {
-      const int64_t s0 = A.ptr[r] - e0, t0 = A.ptr[r + 1] - e0;
-      const int64_t t = t0 < MP_CH ? t0 : MP_CH;
+      if (r != rf) { f0 = A.ptr[r]; f1 = A.ptr[r + 1]; }
+      const int s0 = (int)(f0 - e0);
+      const int64_t t0 = f1 - e0;
+      const int t = (int)(t0 < MP_CH ? t0 : MP_CH);
       T acc = (T)0;
-      for (int64_t q = s0; q < t; ++q) acc += sp[wv][q];
+      for (int q = s0; q < t; q += MP_SUM) {
+        T v[MP_SUM];
+#pragma unroll
+        for (int u = 0; u < MP_SUM; ++u) v[u] = sp[wv][q + u];
+#pragma unroll
+        for (int u = 0; u < MP_SUM; ++u) acc = q + u < t ? acc + v[u] : acc;
+      }
       if (t0 > MP_CH) {
         A.mp_head[c] = acc;                  // finished by mp_cross
       } else {
