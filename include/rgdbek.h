@@ -144,8 +144,9 @@ enum { RGDBEK_SOLVER_AUTO = 0, RGDBEK_SOLVER_CHOL = 1, RGDBEK_SOLVER_CG = 2 };
  * dense column blocks of more than 64 columns when n <= 8192; the blocks
  * are then gathered from these matrices instead of formed from A;
  * CG_SPLIT makes the sparse block projections finish every CG step with
- * separate many-workgroup launches whatever the block size (by default only
- * blocks of more than 16384 indices do; smaller ones finish in the last
+ * separate many-workgroup launches whatever the block size (by default the
+ * whole CG of a single system of moderate size is one launch, and otherwise
+ * only blocks of more than 16384 indices do; smaller ones finish in the last
  * workgroup of the step).  The arithmetic is the same either way.
  * SPARSE_CG keeps the matrix-free CG projections for small sparse single
  * systems (both dimensions up to 4096), which by default, when the inner

@@ -443,6 +443,38 @@ void launch_tall_rowproj_sparse(const Csr<T> &csr, const Csr<T> &csc,
                                 int max_steps, double tol, Ctrl *ctrl,
                                 hipStream_t st);
 
+// One-launch CG of sparse blocks (gridcg.hip; one replica of A, no long
+// segments): vectors of max(m, n) entries and the workgroups' partials.
+template <typename T>
+struct GridCg {
+  T *q = nullptr, *sp = nullptr;    // product; pairs (residual, direction)
+  T *rq = nullptr;                  // pairs of tall row blocks only
+  double *part = nullptr;           // exchange slots, 24 per compute unit
+  unsigned *seq = nullptr;          // exchanges made (columns, rows)
+  unsigned long long *team = nullptr;   // workgroups counted in, team size
+};
+// Empties the exchange slots: before the first launch of every solve.
+template <typename T>
+void launch_grid_clear(GridCg<T> &w, int ncu, hipStream_t st);
+template <typename T>
+bool grid_cg_takes(const Csr<T> &A, const Csr<T> &At, int ncu);
+template <typename T>
+void launch_grid_colproj(const Csr<T> &W, const Csr<T> &At, const int32_t *U,
+                         const int64_t *cnt, int64_t cap, const T *g, T *z,
+                         GridCg<T> &w, int ncu, int max_steps, double tol,
+                         Ctrl *ctrl, hipStream_t st);
+template <typename T>
+void launch_grid_rowproj(const Csr<T> &W, const Csr<T> &A, const int32_t *J,
+                         const int64_t *cnt, int64_t cap, const T *r,
+                         const double *rho, T *x, GridCg<T> &w, T *res, T *v,
+                         int ncu, int max_steps, double tol, Ctrl *ctrl,
+                         hipStream_t st);
+template <typename T>
+void launch_grid_tall(const Csr<T> &A, const Csr<T> &At, const int32_t *J,
+                      const int64_t *cnt, int64_t cap, const T *r, T *x,
+                      GridCg<T> &w, TallWork<T> &tw, int ncu, int max_steps,
+                      double tol, Ctrl *ctrl, hipStream_t st);
+
 // ------------------------------------------------------------ utilities
 template <typename Tout, typename Tin>
 void launch_convert(const Tin *in, Tout *out, int64_t n, hipStream_t st);

@@ -114,6 +114,7 @@ struct Engine {
   TallWork<T> tall;          // row blocks taller than A is wide (CGLS)
   SubWork subc, subr;        // block-restricted CSR (columns U) / CSC (rows J)
   bool tall_rows = false;
+  GridCg<T> gcg;             // one-launch CG of mid-size sparse blocks
   SelectScratch sel;
   Reduce red;
   double *part = nullptr;     // row-residual partials
@@ -493,6 +494,18 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       share = e.m ? (double)e.kr / (double)e.m : 1.0;
       sub(e.subr, at, capr, e.m);
     }
+    // one launch per projection where the segments fit the compute units
+    // (with the block copies: the products take no entry off the block)
+    if (e.subc.idx && e.subr.idx && !(h->p.flags & RGDBEK_FLAG_CG_SPLIT) &&
+        grid_cg_takes<T>(a, at, h->ncu)) {
+      const int64_t len = std::max(e.m, e.n) + 64;
+      e.gcg.q = P.alloc<T>(len);
+      e.gcg.sp = P.alloc<T>(2 * len);
+      if (e.tall_rows) e.gcg.rq = P.alloc<T>(2 * len);
+      e.gcg.part = P.alloc<double>(24 * h->ncu, false);
+      e.gcg.seq = P.alloc<unsigned>(2);
+      e.gcg.team = P.alloc<unsigned long long>(4);
+    }
     // Small single systems: the Gram matrices of all columns and all rows,
     // formed once through a dense copy, turn each block projection into a
     // gather, one Cholesky or persistent PCG launch and one sparse update,
@@ -691,11 +704,13 @@ void pcg_solve(rgdbek_ctx *h, T *G, int64_t cap, const int64_t *cnt,
     launch_pcg_gram_step<T>(G, cap, cnt, y, w, k, itol, h->ctrl, ph, 1, h->st);
 }
 
-// The persistent PCG's exchange buffers start every solve empty.
+// The exchange buffers of the persistent CGs start every solve empty.
 template <typename T>
-void clear_exchange(Engine<T> &e, hipStream_t st) {
+void clear_exchange(rgdbek_ctx *h, Engine<T> &e) {
+  hipStream_t st = h->st;
   if (e.cgc.xch) launch_pcg_clear<T>(e.cgc, st);
   if (e.cgr.xch) launch_pcg_clear<T>(e.cgr, st);
+  if (e.gcg.part) launch_grid_clear<T>(e.gcg, h->ncu, st);
 }
 
 template <typename T>
@@ -799,7 +814,11 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     const Csr<T> wcsr = e.subc.idx ? launch_sub_matrix<T>(e.csr, e.U, cntU, e.kc,
                                                           e.subc, c, st)
                                    : e.csr;
-    launch_sparse_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.scc,
+    if (e.gcg.q)
+      launch_grid_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.gcg,
+                             h->ncu, maxs, itol, c, st);
+    else
+      launch_sparse_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.scc,
                              maxs, itol, c, 1, st);
   }
   // ---- row phase: r = b - z - A x, eps^x, stop test, select J, project x
@@ -848,6 +867,9 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     if (e.dense)
       launch_tall_rowproj_dense<T>(e.arm, e.J, cntJ, e.kr, e.r, e.x, e.tall,
                                    e.upd, maxs, itol, c, st);
+    else if (e.gcg.q)
+      launch_grid_tall<T>(e.csr, e.csc, e.J, cntJ, e.kr, e.r, e.x, e.gcg,
+                          e.tall, h->ncu, maxs, itol, c, st);
     else
       launch_tall_rowproj_sparse<T>(e.csr, e.csc, e.J, cntJ, e.kr, e.r, e.x,
                                     e.tall, maxs, itol, c, st);
@@ -905,7 +927,12 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     const Csr<T> wcsc = e.subr.idx ? launch_sub_matrix<T>(e.csc, e.J, cntJ, e.kr,
                                                           e.subr, c, st)
                                    : e.csc;
-    launch_sparse_rowproj<T>(e.csr, wcsc, e.J, cntJ, e.kr, e.r, e.rho, e.x,
+    if (e.gcg.q)
+      launch_grid_rowproj<T>(wcsc, e.csr, e.J, cntJ, e.kr, e.r, e.rho, e.x,
+                             e.gcg, e.scr.res, e.scr.v, h->ncu, maxs, itol, c,
+                             st);
+    else
+      launch_sparse_rowproj<T>(e.csr, wcsc, e.J, cntJ, e.kr, e.r, e.rho, e.x,
                              e.scr, maxs, itol, c, 1, st);
   }
   ProfScope ps(h, RGDBEK_PROF_STOP);
@@ -1042,7 +1069,7 @@ rgdbek_status solve64(rgdbek_ctx *h, Engine<double> &e, int which,
   }
   check_b(h, b, e.m);
   prof_begin_solve(h);
-  clear_exchange(e, st);
+  clear_exchange(h, e);
   HIPCHK(hipMemcpyAsync(e.b, b, sizeof(double) * e.m, hipMemcpyDeviceToDevice, st));
   if (resume) {
     HIPCHK(hipMemcpyAsync(e.x, x, sizeof(double) * e.n, hipMemcpyDeviceToDevice, st));
@@ -1120,7 +1147,7 @@ rgdbek_status solve_mixed(rgdbek_ctx *h, const double *b, double *x,
   check_b(h, b, E.m);
   prof_begin_solve(h);
   HIPCHK(hipMemcpyAsync(E.b, b, sizeof(double) * E.m, hipMemcpyDeviceToDevice, st));
-  clear_exchange(F, st);
+  clear_exchange(h, F);
   launch_axpby<double, double>(E.n, 0.0, h->x64, 0.0, (const double *)nullptr, st);
   HIPCHK(hipMemcpyAsync(h->z64, b, sizeof(double) * E.m, hipMemcpyDeviceToDevice, st));
   if (E.nseg) {
