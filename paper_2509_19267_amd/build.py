@@ -18,7 +18,7 @@ LIBNAME = "librgdbek.so"
 ARCH = "gfx950"
 
 SOURCES = ["select.hip", "spmv.hip", "proj.hip", "pcg.hip", "chol.hip",
-           "gridcg.hip", "utils.hip", "batch.hip",
+           "gridcg.hip", "balprod.hip", "utils.hip", "batch.hip",
            "rep.hip", "runtime.hip"]
 # Bit-exact selection needs unfused, correctly rounded FP64 operations.
 EXTRA = {"select.hip": ["-ffp-contract=off"]}

@@ -130,7 +130,7 @@ struct Csr {                 // CSR (or CSC viewed as CSR of the transpose)
   // spanning chunks are listed (mp_xrow, first/last chunk) and finished by a
   // second launch from per-chunk head/lead partials.
   const int32_t *mp_rs = nullptr;
-  int64_t mp_nchunk = 0;
+  int64_t mp_nchunk = 0, mp_maxrows = 0;   // most rows of one chunk
   const int32_t *mp_xrow = nullptr, *mp_xcs = nullptr, *mp_xce = nullptr;
   int64_t mp_ncross = 0;
   T *mp_head = nullptr, *mp_lead = nullptr;   // nchunk each
@@ -412,6 +412,38 @@ struct SubWork {
   int64_t cap = 0;           // entry capacity
   int group = 1;             // lanes per row for the compact matrix
 };
+// Sparse CG products balanced by nonzeros (balprod.hip): copies of the
+// block's entries in a SubWork per direction, and what a product does with
+// its sums.
+enum { BP_COL_WIDE = 0, BP_COL_NARROW = 1, BP_ROW_WIDE = 2, BP_ROW_NARROW = 3 };
+int64_t bal_blocks(int64_t nchunk);
+template <typename T>
+void launch_bal_fill(const Csr<T> &A, int wide, const int32_t *mask,
+                     SubWork &w, Ctrl *ctrl, hipStream_t st);
+template <typename T>
+void launch_bal_prod(const Csr<T> &A, int epi, const SubWork &w, const T *vec,
+                     T *out, T *x, const int32_t *pos, const T *p, int64_t m,
+                     double *part, const double *qpart, int nq, int step,
+                     Ctrl *ctrl, hipStream_t st);
+// Block projections with those products (mask: one flag per column or row of
+// the block's dimension, zero between calls; w.pos of that dimension).
+template <typename T>
+bool balanced_cg_takes(const Csr<T> &csr, const Csr<T> &csc, int64_t cap,
+                       int64_t part_cap);
+template <typename T>
+void launch_balanced_colproj(const Csr<T> &csr, const Csr<T> &csc,
+                             SubWork &wr, SubWork &wc, int32_t *mask,
+                             const int32_t *U, const int64_t *count_dev,
+                             int64_t cap, const T *g, T *z, SparseCg<T> &w,
+                             int max_steps, double tol, Ctrl *ctrl,
+                             hipStream_t st);
+template <typename T>
+void launch_balanced_rowproj(const Csr<T> &csr, const Csr<T> &csc,
+                             SubWork &wr, SubWork &wc, int32_t *mask,
+                             const int32_t *J, const int64_t *count_dev,
+                             int64_t cap, const T *r, const double *rho, T *x,
+                             SparseCg<T> &w, int max_steps, double tol,
+                             Ctrl *ctrl, hipStream_t st);
 template <typename T>
 Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
                          const int64_t *count_dev, int64_t list_cap,

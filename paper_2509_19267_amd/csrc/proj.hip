@@ -1848,6 +1848,137 @@ Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
   B.mp_nchunk = 0;
   return B;
 }
+// ------------------------------------------------------------ balanced CG
+// The block projections of one stored matrix with products balanced by
+// nonzeros.  wr and wc hold the block's entries by rows and by columns.
+//
+// Taken wherever a block has more than BAL_MIN_CAP indices, because it was
+// faster over all of its range on power-law rows (8 iterations, row split /
+// balanced, ms): 10000 x 5000 at 1 % blocks 2.19 / 2.14 and at 50 % 4.13 /
+// 3.08, 100000 x 50000 at 10 % 4.83 / 3.24, 1M x 500K at 10 % 13.4 / 11.3 and
+// at 50 % 32.1 / 20.9; on 96 grid systems 272 / 253.  Below that the visit of
+// all rows costs more than the block (3000 x 1500 at 1 %: 1.90 / 1.96).  Not
+// for even rows of 64 entries and more (no long segments), where a wave per
+// row is already balanced (40000 x 20000, 1 % dense: 208 / 219), nor where a
+// workgroup would get many thousand (empty) rows, which are not spread.
+constexpr int64_t BAL_MIN_CAP = 32;
+constexpr int64_t BAL_MAX_ROWS = 1024;         // of one chunk of the plan
+template <typename T>
+bool balanced_cg_takes(const Csr<T> &csr, const Csr<T> &csc, int64_t cap,
+                       int64_t part_cap) {
+  if (csr.rep != 1 || !csr.mp_rs || !csc.mp_rs || cap <= BAL_MIN_CAP)
+    return false;
+  if (csr.group == 64 && csc.group == 64 && !csr.nlong && !csc.nlong)
+    return false;
+  if (std::max(csr.mp_maxrows, csc.mp_maxrows) > BAL_MAX_ROWS) return false;
+  // the copies' and the partials' room
+  const int64_t nb = bal_blocks(std::max(csr.mp_nchunk, csc.mp_nchunk));
+  return nb + 4 * (int64_t)SC_SUM_MAX <= part_cap &&
+         2 * nb <= std::min(csr.rows, csc.rows);
+}
+template <typename T>
+static void bal_copies(const Csr<T> &wide, SubWork &ww, const Csr<T> &narrow,
+                       SubWork &wn, int32_t *mask, const int32_t *list,
+                       const int64_t *count_dev, int64_t cap, Ctrl *ctrl,
+                       hipStream_t st) {
+  const unsigned gm = (unsigned)std::min<int64_t>(
+      std::max<int64_t>((cap + SB_NT - 1) / SB_NT, 1), 1024);
+  hipLaunchKernelGGL(sub_mark, dim3(gm), dim3(SB_NT), 0, st, list, count_dev,
+                     mask, 1, ctrl);
+  launch_bal_fill<T>(wide, 1, mask, ww, ctrl, st);
+  launch_bal_fill<T>(narrow, 0, mask, wn, ctrl, st);
+  hipLaunchKernelGGL(sub_mark, dim3(gm), dim3(SB_NT), 0, st, list, count_dev,
+                     mask, 0, ctrl);
+}
+template <typename T>
+void launch_balanced_colproj(const Csr<T> &csr, const Csr<T> &csc,
+                             SubWork &wr, SubWork &wc, int32_t *mask,
+                             const int32_t *U, const int64_t *count_dev,
+                             int64_t cap, const T *g, T *z, SparseCg<T> &w,
+                             int max_steps, double tol, Ctrl *ctrl,
+                             hipStream_t st) {
+  bal_copies<T>(csr, wr, csc, wc, mask, U, count_dev, cap, ctrl, st);
+  sc_start<T>(U, count_dev, cap, g, (const double *)nullptr, (T *)nullptr, w,
+              w.pos, 1, ctrl, 0, 1, st);
+  const int64_t nw = bal_blocks(csr.mp_nchunk), nn = bal_blocks(csc.mp_nchunk);
+  // partials added up by the next launch where they are few, as above
+  const bool sum_w = nw <= SC_SUM_MAX, sum_n = nn <= SC_SUM_MAX;
+  double *pn = sum_n ? w.part + (w.part_cap - 4 * (int64_t)SC_SUM_MAX) : w.part;
+  if (!sum_n && sum_w) pn = w.part + SC_SUM_MAX;
+  const unsigned nbu = sc_list_blocks(cap);
+  for (int s = 0; s < max_steps; ++s) {
+    launch_bal_prod<T>(csr, BP_COL_WIDE, wr, w.phat, w.wide, (T *)nullptr,
+                       nullptr, (const T *)nullptr, 0, w.part, nullptr, 0, s,
+                       ctrl, st);
+    if (!sum_w)
+      hipLaunchKernelGGL(sc_wide_col_fin<T>, dim3(1), dim3(1024), 0, st,
+                         (const double *)w.part, nw, (const double *)nullptr,
+                         (int64_t)0, s, ctrl, 1);
+    launch_bal_prod<T>(csc, BP_COL_NARROW, wc, w.wide, w.res, z, w.pos,
+                       (const T *)nullptr, csr.rows, pn, w.part,
+                       sum_w ? (int)nw : 0, s, ctrl, st);
+    if (!sum_n)
+      hipLaunchKernelGGL(sc_narrow_col_fin, dim3(1), dim3(1024), 0, st,
+                         (const double *)pn, nn, (const double *)nullptr,
+                         (int64_t)0, tol, s, ctrl, 1);
+    hipLaunchKernelGGL(sc_cupd<T>, dim3(nbu), dim3(SC_NT), 0, st, U, count_dev,
+                       w.res, w.p, w.phat, (const double *)pn,
+                       sum_n ? (int)nn : 0, tol, ctrl, s, 1);
+  }
+  hipLaunchKernelGGL(sc_clear<T>, dim3(nbu), dim3(SC_NT), 0, st, U, count_dev,
+                     cap, w.phat, w.pos, ctrl, 1);
+}
+template <typename T>
+void launch_balanced_rowproj(const Csr<T> &csr, const Csr<T> &csc,
+                             SubWork &wr, SubWork &wc, int32_t *mask,
+                             const int32_t *J, const int64_t *count_dev,
+                             int64_t cap, const T *r, const double *rho, T *x,
+                             SparseCg<T> &w, int max_steps, double tol,
+                             Ctrl *ctrl, hipStream_t st) {
+  bal_copies<T>(csc, wc, csr, wr, mask, J, count_dev, cap, ctrl, st);
+  sc_start<T>(J, count_dev, cap, r, rho, w.v, w, w.pos, 1, ctrl, 1, 1, st);
+  const int64_t nn = bal_blocks(csr.mp_nchunk);
+  const bool sum_n = nn <= SC_SUM_MAX;
+  double *pu = w.part + (w.part_cap - 4 * (int64_t)SC_SUM_MAX);
+  const unsigned nbu = sc_list_blocks(cap);
+  for (int s = 0; s < max_steps; ++s) {
+    launch_bal_prod<T>(csc, BP_ROW_WIDE, wc, w.phat, w.wide, x, nullptr,
+                       (const T *)nullptr, 0, (double *)nullptr, nullptr, 0, s,
+                       ctrl, st);
+    launch_bal_prod<T>(csr, BP_ROW_NARROW, wr, w.wide, w.v + cap, (T *)nullptr,
+                       w.pos, w.p, 0, w.part, nullptr, 0, s, ctrl, st);
+    if (!sum_n)
+      hipLaunchKernelGGL(sc_narrow_row_fin, dim3(1), dim3(1024), 0, st,
+                         (const double *)w.part, nn, (const double *)nullptr,
+                         (int64_t)0, s, ctrl, 1);
+    hipLaunchKernelGGL(sc_rupd1<T>, dim3(nbu), dim3(SC_NT), 0, st, J,
+                       count_dev, rho, w.res, w.v, w.v + cap,
+                       (const double *)w.part, sum_n ? (int)nn : 0, pu, ctrl,
+                       s, 1);
+    hipLaunchKernelGGL(sc_rupd2<T>, dim3(nbu), dim3(SC_NT), 0, st, J,
+                       count_dev, w.v, w.p, w.phat, (const double *)pu,
+                       (int)nbu, tol, ctrl, s, 1);
+  }
+  hipLaunchKernelGGL(sc_row_finish<T>,
+                     dim3((unsigned)((csc.rows + SC_NT - 1) / SC_NT)),
+                     dim3(SC_NT), 0, st, csc.rows, w.wide, x, ctrl, 1);
+  hipLaunchKernelGGL(sc_clear<T>, dim3(nbu), dim3(SC_NT), 0, st, J, count_dev,
+                     cap, w.phat, w.pos, ctrl, 1);
+}
+#define INST_BAL(T)                                                           \
+  template bool balanced_cg_takes<T>(const Csr<T> &, const Csr<T> &, int64_t, \
+                                     int64_t);                                \
+  template void launch_balanced_colproj<T>(                                   \
+      const Csr<T> &, const Csr<T> &, SubWork &, SubWork &, int32_t *,        \
+      const int32_t *, const int64_t *, int64_t, const T *, T *,              \
+      SparseCg<T> &, int, double, Ctrl *, hipStream_t);                       \
+  template void launch_balanced_rowproj<T>(                                   \
+      const Csr<T> &, const Csr<T> &, SubWork &, SubWork &, int32_t *,        \
+      const int32_t *, const int64_t *, int64_t, const T *, const double *,   \
+      T *, SparseCg<T> &, int, double, Ctrl *, hipStream_t);
+INST_BAL(double)
+INST_BAL(float)
+
 template Csr<double> launch_sub_matrix<double>(const Csr<double> &, const int32_t *, const int64_t *, int64_t, SubWork &, Ctrl *, hipStream_t);
 template Csr<float> launch_sub_matrix<float>(const Csr<float> &, const int32_t *, const int64_t *, int64_t, SubWork &, Ctrl *, hipStream_t);
 

@@ -54,7 +54,7 @@ int pick_group(double mean_len) {
 struct MergePlan {
   int32_t *rs = nullptr;                 // nchunk + 1 owned-row starts
   int32_t *xrow = nullptr, *xcs = nullptr, *xce = nullptr;
-  int64_t nchunk = 0, ncross = 0;
+  int64_t nchunk = 0, ncross = 0, maxrows = 0;
 };
 
 // Row groups of the many-right-hand-side products of one CSR (see rep.hip).
@@ -115,6 +115,7 @@ struct Engine {
   SubWork subc, subr;        // block-restricted CSR (columns U) / CSC (rows J)
   bool tall_rows = false;
   GridCg<T> gcg;             // one-launch CG of mid-size sparse blocks
+  bool bal_c = false, bal_r = false;   // nonzero-balanced CG of larger ones
   SelectScratch sel;
   Reduce red;
   double *part = nullptr;     // row-residual partials
@@ -372,6 +373,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       auto plan = [&](Csr<T> &c, const MergePlan &mp) {
         c.mp_rs = mp.rs;
         c.mp_nchunk = mp.nchunk;
+        c.mp_maxrows = mp.maxrows;
         c.mp_xrow = mp.xrow;
         c.mp_xcs = mp.xcs;
         c.mp_xce = mp.xce;
@@ -505,6 +507,20 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       e.gcg.part = P.alloc<double>(24 * h->ncu, false);
       e.gcg.seq = P.alloc<unsigned>(2);
       e.gcg.team = P.alloc<unsigned long long>(4);
+    }
+    // larger ones: products balanced by nonzeros
+    if (e.subc.idx && e.subr.idx && !(h->p.flags & RGDBEK_FLAG_CG_SPLIT) &&
+        !e.gcg.q) {
+      e.bal_c = balanced_cg_takes<T>(a, at, e.kc, e.scc.part_cap);
+      e.bal_r = !e.tall_rows &&
+                balanced_cg_takes<T>(a, at, e.kr, e.scr.part_cap);
+      for (int ph = 0; ph < 2; ++ph) {
+        SparseCg<T> &sc = ph == 0 ? e.scc : e.scr;
+        if (!(ph == 0 ? e.bal_c : e.bal_r) || sc.pos) continue;
+        const int64_t d = ph == 0 ? e.n : e.m;
+        sc.pos = P.alloc<int32_t>(d, false);
+        HIPCHK(hipMemsetAsync(sc.pos, 0xff, sizeof(int32_t) * d, h->st));
+      }
     }
     // Small single systems: the Gram matrices of all columns and all rows,
     // formed once through a dense copy, turn each block projection into a
@@ -811,10 +827,15 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
                                   e.z, c, 1, st);
   } else {
     ProfScope ps(h, RGDBEK_PROF_COL_SOLVE, 0);
-    const Csr<T> wcsr = e.subc.idx ? launch_sub_matrix<T>(e.csr, e.U, cntU, e.kc,
-                                                          e.subc, c, st)
-                                   : e.csr;
-    if (e.gcg.q)
+    const Csr<T> wcsr =
+        e.subc.idx && !e.bal_c
+            ? launch_sub_matrix<T>(e.csr, e.U, cntU, e.kc, e.subc, c, st)
+            : e.csr;
+    if (e.bal_c)
+      launch_balanced_colproj<T>(e.csr, e.csc, e.subc, e.subr, e.subc.mask,
+                                 e.U, cntU, e.kc, e.g, e.z, e.scc, maxs, itol,
+                                 c, st);
+    else if (e.gcg.q)
       launch_grid_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.gcg,
                              h->ncu, maxs, itol, c, st);
     else
@@ -924,10 +945,15 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
                                   e.x, c, 1, st);
   } else {
     ProfScope ps(h, RGDBEK_PROF_ROW_SOLVE, 1);
-    const Csr<T> wcsc = e.subr.idx ? launch_sub_matrix<T>(e.csc, e.J, cntJ, e.kr,
-                                                          e.subr, c, st)
-                                   : e.csc;
-    if (e.gcg.q)
+    const Csr<T> wcsc =
+        e.subr.idx && !e.bal_r
+            ? launch_sub_matrix<T>(e.csc, e.J, cntJ, e.kr, e.subr, c, st)
+            : e.csc;
+    if (e.bal_r)
+      launch_balanced_rowproj<T>(e.csr, e.csc, e.subc, e.subr, e.subr.mask,
+                                 e.J, cntJ, e.kr, e.r, e.rho, e.x, e.scr, maxs,
+                                 itol, c, st);
+    else if (e.gcg.q)
       launch_grid_rowproj<T>(wcsc, e.csr, e.J, cntJ, e.kr, e.r, e.rho, e.x,
                              e.gcg, e.scr.res, e.scr.v, h->ncu, maxs, itol, c,
                              st);
@@ -1448,6 +1474,8 @@ void build_merge_plan(rgdbek_ctx *h, const int64_t *ptr_dev, int64_t rows,
     }
   }
   mp->nchunk = nch;
+  for (int64_t c = 0; c < nch; ++c)
+    mp->maxrows = std::max<int64_t>(mp->maxrows, rs[c + 1] - rs[c]);
   mp->ncross = (int64_t)xr.size();
   auto up = [&](const std::vector<int32_t> &v) {
     int32_t *d = h->pool.alloc<int32_t>(std::max<int64_t>(1, (int64_t)v.size()), false);
