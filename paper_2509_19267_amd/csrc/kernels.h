@@ -253,7 +253,8 @@ void launch_err_ref(int64_t n, const T *x, const double *x_ref,
                     int respect_done, hipStream_t st);
 // Ctrl::ref2 = sum v_i^2 (FP64), one workgroup.
 template <typename T>
-void launch_set_ref2(int64_t n, const T *v, Ctrl *ctrl, hipStream_t st);
+void launch_set_ref2(int64_t n, const T *v, double *part, Ctrl *ctrl,
+                     hipStream_t st);   // part: 1024
 void launch_stop_rowres(const double *part, int nparts, Ctrl *ctrl,
                         hipStream_t st);
 void launch_end_iter(Ctrl *ctrl, hipStream_t st);

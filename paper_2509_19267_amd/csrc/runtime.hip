@@ -588,7 +588,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
     e.iid.ctot = P.alloc<uint64_t>(select_iid_chunks(dmax) + 64);
     e.iid.flags = P.alloc<int32_t>(dmax + 64);
   }
-  e.red.part = P.alloc<double>(1024);
+  e.red.part = P.alloc<double>(1024);   // also of launch_set_ref2
   e.red.cap = 1024;
   if (h->nseg) {
     e.seltmp = P.alloc<int32_t>(std::max(e.kc, e.kr) + 64);
@@ -1105,8 +1105,10 @@ rgdbek_status solve64(rgdbek_ctx *h, Engine<double> &e, int which,
     HIPCHK(hipMemcpyAsync(e.z, b, sizeof(double) * e.m, hipMemcpyDeviceToDevice, st));
   }
   ctrl_reset(h, it0, h->p.max_iter, stop, h->p.tol);
-  if (stop == RGDBEK_STOP_ERR_REF) launch_set_ref2<double>(e.n, x_ref, h->ctrl, st);
-  else launch_set_ref2<double>(e.m, e.b, h->ctrl, st);
+  if (stop == RGDBEK_STOP_ERR_REF)
+    launch_set_ref2<double>(e.n, x_ref, e.red.part, h->ctrl, st);
+  else
+    launch_set_ref2<double>(e.m, e.b, e.red.part, h->ctrl, st);
   if (e.nseg) {
     launch_seg_reset(e.seg, e.nseg, it0, 0, nullptr, st);
     if (stop == RGDBEK_STOP_ERR_REF) launch_seg_ref2<double>(x_ref, e.seg, e.nseg, 1, st);
@@ -1244,10 +1246,10 @@ rgdbek_status solve_mixed(rgdbek_ctx *h, const double *b, double *x,
       launch_seg_fold(E.seg, E.nseg, h->ctrl, 0, h->p.max_iter, 1, st);
       launch_seg_converged(E.seg, E.nseg, h->fixed, st);
     } else if (test_now && stop == RGDBEK_STOP_ERR_REF) {
-      launch_set_ref2<double>(E.n, x_ref, h->ctrl, st);
+      launch_set_ref2<double>(E.n, x_ref, E.red.part, h->ctrl, st);
       launch_err_ref<double>(E.n, h->x64, x_ref, nullptr, E.red, h->ctrl, 0, st);
     } else if (test_now) {
-      launch_set_ref2<double>(E.m, E.b, h->ctrl, st);
+      launch_set_ref2<double>(E.m, E.b, E.red.part, h->ctrl, st);
       launch_stop_rowres(E.part, nparts, h->ctrl, st);
     }
     }
@@ -1279,7 +1281,7 @@ rgdbek_status solve_mixed(rgdbek_ctx *h, const double *b, double *x,
       HIPCHK(hipMemcpyAsync(&h->ctrl->pass_drop, &h->hctrl->pass_drop,
                             sizeof(double), hipMemcpyHostToDevice, st));
     }
-    launch_set_ref2<double>(E.m, E.b, h->ctrl, st);
+    launch_set_ref2<double>(E.m, E.b, E.red.part, h->ctrl, st);
     if (E.nseg) {
       launch_seg_reset(E.seg, E.nseg, 0, 1, h->fixed, st);
       launch_seg_ref2<double>(E.b, E.seg, E.nseg, 0, st);

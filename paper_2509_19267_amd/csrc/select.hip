@@ -434,21 +434,21 @@ sel_small(const T *__restrict__ eps, int64_t d, int64_t k, double floor,
 // and the threshold search and ordered compaction (one workgroup each).
 // Local indices go to tmp[koff_s ..]; counts to cnt[s].
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(WG_NT)
 sel_seg_max(const T *__restrict__ eps, const SegInfo *__restrict__ seg, int ph,
             double *__restrict__ segmax, Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   const SegInfo &g = seg[blockIdx.x];
   if (g.done) return;
-  __shared__ double sh[256 / WAVE];
+  __shared__ double sh[WG_NT / WAVE];
   const int64_t off = ph == 0 ? g.col_off : g.row_off;
   const int64_t d = ph == 0 ? g.ncol : g.nrow;
   double mx = 0.0;
-  for (int64_t j0 = threadIdx.x; j0 < d; j0 += WG_UNROLL * 256) {
+  for (int64_t j0 = threadIdx.x; j0 < d; j0 += WG_UNROLL * WG_NT) {
     double e[WG_UNROLL];
 #pragma unroll
     for (int u = 0; u < WG_UNROLL; ++u) {
-      const int64_t j = j0 + (int64_t)u * 256;
+      const int64_t j = j0 + (int64_t)u * WG_NT;
       e[u] = j < d ? (double)eps[off + j] : 0.0;
     }
 #pragma unroll
@@ -459,7 +459,7 @@ sel_seg_max(const T *__restrict__ eps, const SegInfo *__restrict__ seg, int ph,
   if ((threadIdx.x & (WAVE - 1)) == 0) sh[threadIdx.x / WAVE] = mx;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int i = 0; i < 256 / WAVE; ++i) mx = sh[i] > mx ? sh[i] : mx;
+    for (int i = 0; i < WG_NT / WAVE; ++i) mx = sh[i] > mx ? sh[i] : mx;
     segmax[blockIdx.x] = mx;
   }
 }
@@ -543,14 +543,16 @@ sel_seg_resolve(const SegInfo *__restrict__ seg, int ph,
 }
 
 // Concatenate the per-system draws into one list of global indices and set
-// Ctrl::sel_count[ph] to the total.
+// Ctrl::sel_count[ph] to the total.  (Several workgroups per system: with
+// one, a loop of dependent loads and stores, 64 systems of 131072 rows took
+// 46 us and 12 grid systems 11 us; now 20 and 4.5.)
 __global__ void __launch_bounds__(256)
 sel_seg_pack(const SegInfo *__restrict__ seg, int nseg, int ph,
              const int32_t *__restrict__ tmp, const int64_t *__restrict__ cnt,
              int32_t *__restrict__ out, Ctrl *ctrl, int respect_done) {
   if (respect_done && ctrl_done(ctrl)) return;
   __shared__ int64_t sh64[256 / WAVE];
-  const int s = blockIdx.x;
+  const int s = blockIdx.y;
   int64_t before = 0, total = 0;
   for (int q = threadIdx.x; q < nseg; q += 256) {
     total += cnt[q];
@@ -562,9 +564,10 @@ sel_seg_pack(const SegInfo *__restrict__ seg, int nseg, int ph,
   const int64_t off = ph == 0 ? g.col_off : g.row_off;
   const int64_t ko = ph == 0 ? g.kc_off : g.kr_off;
   const int64_t c = cnt[s];
-  for (int64_t a = threadIdx.x; a < c; a += 256)
+  for (int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x; a < c;
+       a += (int64_t)gridDim.x * 256)
     out[before + a] = (int32_t)(tmp[ko + a] + off);
-  if (s == 0 && threadIdx.x == 0) ctrl->sel_count[ph] = total;
+  if (s == 0 && blockIdx.x == 0 && threadIdx.x == 0) ctrl->sel_count[ph] = total;
 }
 
 // ------------------------------------------------ multi-workgroup selection
@@ -1738,7 +1741,7 @@ void launch_select_seg(const T *eps, const SegInfo *seg, int nseg, int ph,
                        double *segmax, int32_t *tmp, int64_t *cnt,
                        int32_t *out, Ctrl *ctrl, int respect_done,
                        hipStream_t st) {
-  hipLaunchKernelGGL(sel_seg_max<T>, dim3(nseg), dim3(256), 0, st, eps, seg,
+  hipLaunchKernelGGL(sel_seg_max<T>, dim3(nseg), dim3(WG_NT), 0, st, eps, seg,
                      ph, segmax, ctrl, respect_done);
   const unsigned gx = (unsigned)((dmax + 4 * 256 - 1) / (4 * 256));
   hipLaunchKernelGGL(sel_seg_keys<T>, dim3(gx > 0 ? gx : 1, nseg), dim3(256),
@@ -1746,7 +1749,8 @@ void launch_select_seg(const T *eps, const SegInfo *seg, int nseg, int ph,
                      keys, ctrl, respect_done);
   hipLaunchKernelGGL(sel_seg_resolve, dim3(nseg), dim3(WG_NT), 0, st, seg, ph,
                      keys, tmp, cnt, ctrl, respect_done);
-  hipLaunchKernelGGL(sel_seg_pack, dim3(nseg), dim3(256), 0, st, seg, nseg, ph,
+  hipLaunchKernelGGL(sel_seg_pack, dim3(gx > 0 ? gx : 1, nseg), dim3(256), 0,
+                     st, seg, nseg, ph,
                      tmp, cnt, out, ctrl, respect_done);
 }
 template void launch_select_seg<double>(const double *, const SegInfo *, int,

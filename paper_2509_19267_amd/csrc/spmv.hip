@@ -12,6 +12,8 @@
 // iteration can share the pass); 16-byte loads, each wave streams whole row
 // segments, column partials meet in LDS, row-block partials are summed in a
 // fixed order by the finalise kernel.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -714,26 +716,38 @@ template void launch_err_ref<float>(int64_t, const float *, const double *,
                                     const double *, Reduce &, Ctrl *, int,
                                     hipStream_t);
 
+// Ctrl::ref2 = ||v||^2.  One workgroup's loop of loads took 3.2 ms for 64
+// images of 131072 rows; up to R2_MAXB workgroups leave partials instead, the
+// last one adds them in order.
+constexpr int R2_MAXB = 1024;
 template <typename T>
-__global__ void __launch_bounds__(1024)
-set_ref2_kernel(int64_t n, const T *__restrict__ v, Ctrl *ctrl) {
-  __shared__ double sh[1024 / WAVE];
+__global__ void __launch_bounds__(256)
+set_ref2_kernel(int64_t n, const T *__restrict__ v, double *part, Ctrl *ctrl) {
+  __shared__ double sh[256 / WAVE];
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 1024) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * 256) {
     const double a = (double)v[i];
     s += a * a;
   }
-  s = block_sum<1024>(s, sh);
+  s = block_sum<256>(s, sh);
+  if (threadIdx.x == 0) st_agent(&part[blockIdx.x], s);
+  if (!last_block(&ctrl->ticket[1])) return;
+  s = 0.0;
+  for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) s += ld_agent(&part[b]);
+  s = block_sum<256>(s, sh);
   if (threadIdx.x == 0) ctrl->ref2 = s;
 }
 template <typename T>
-void launch_set_ref2(int64_t n, const T *v, Ctrl *ctrl, hipStream_t st) {
-  hipLaunchKernelGGL(set_ref2_kernel<T>, dim3(1), dim3(1024), 0, st, n, v,
-                     ctrl);
+void launch_set_ref2(int64_t n, const T *v, double *part, Ctrl *ctrl,
+                     hipStream_t st) {
+  const int64_t nb = std::min<int64_t>(R2_MAXB, std::max<int64_t>(1, (n + 1023) / 1024));
+  hipLaunchKernelGGL(set_ref2_kernel<T>, dim3((unsigned)nb), dim3(256), 0, st,
+                     n, v, part, ctrl);
 }
-template void launch_set_ref2<double>(int64_t, const double *, Ctrl *,
+template void launch_set_ref2<double>(int64_t, const double *, double *, Ctrl *,
                                       hipStream_t);
-template void launch_set_ref2<float>(int64_t, const float *, Ctrl *,
+template void launch_set_ref2<float>(int64_t, const float *, double *, Ctrl *,
                                      hipStream_t);
 
 // RSE  : sum(b - Ax)^2 / ||b||^2 <= tol
