@@ -159,10 +159,84 @@ gram_mfma_kernel(const T *__restrict__ X, int64_t ld, int64_t len,
       }
 }
 
+// The same for blocks of few tiles.  c = 250 gives 10 tiles of 64 x 64, whose
+// workgroups walk the rows' length in stages of 16 as one chain (55 us at
+// length 501); here a workgroup has one 16 x 16 tile and its waves share the
+// length, each with GS_DEPTH independent steps of 16 in flight, straight from
+// memory (a lane reads four consecutive k of row l % 16, the inner dimension
+// in the same order for both operands); their sums meet in LDS.
+constexpr int GS_W = 4;              // waves per tile
+constexpr int GS_DEPTH = 4;
+// Whole solves with the 64 x 64 tiles / these: 500 x 250 systems 38.9 / 33.8
+// ms, 2003 x 501 in blocks of 175 76.6 / 66.3, 4000 x 1000 of 350 93.3 / 76.9
+// and of 600 59.9 / 51.7.  Blocks of 2000 read their rows too often: 13.4 /
+// 12.0 ms at length 2500, but 27.2 / 29.6 at 6000.
+constexpr int64_t GS_MAX = 1024;
+template <typename T>
+__global__ void __launch_bounds__(GS_W * WAVE)
+gram_small_kernel(const T *__restrict__ X, int64_t ld, int64_t len,
+                  const int32_t *__restrict__ list,
+                  const int64_t *__restrict__ cnt, int64_t ldg,
+                  T *__restrict__ G, Ctrl *ctrl, int respect_done) {
+  if (respect_done && ctrl_done(ctrl)) return;
+  typedef typename Mfma16<T>::v4 v4;
+  const int64_t c = *cnt;
+  const int64_t ta = (int64_t)blockIdx.y * 16, tb = (int64_t)blockIdx.x * 16;
+  if (ta >= c || tb >= c || tb > ta) return;   // lower tiles only
+  __shared__ T sh[GS_W][4][WAVE];
+  const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+  const int lr = lane & 15, lk = lane >> 4;
+  const T *xa = X + (int64_t)list[ta + lr < c ? ta + lr : c - 1] * ld;
+  const T *xb = X + (int64_t)list[tb + lr < c ? tb + lr : c - 1] * ld;
+  v4 acc = (v4){0, 0, 0, 0};
+  for (int64_t k0 = 16 * w; k0 < len; k0 += 16 * GS_W * GS_DEPTH) {
+    v4 a[GS_DEPTH], b[GS_DEPTH];
+#pragma unroll
+    for (int d = 0; d < GS_DEPTH; ++d) {
+      const int64_t k = k0 + (int64_t)16 * GS_W * d + 4 * lk;
+      if (k + 4 <= len) {            // rows are 16-byte aligned, padded to 8
+        a[d] = *reinterpret_cast<const v4 *>(xa + k);
+        b[d] = *reinterpret_cast<const v4 *>(xb + k);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          a[d][u] = k + u < len ? xa[k + u] : (T)0;
+          b[d][u] = k + u < len ? xb[k + u] : (T)0;
+        }
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < GS_DEPTH; ++d)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        acc = Mfma16<T>::mma(a[d][u], b[d][u], acc);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) sh[w][u][lane] = acc[u];
+  __syncthreads();
+  // wave u finishes accumulator element u
+  T v = (T)0;
+#pragma unroll
+  for (int q = 0; q < GS_W; ++q) v += sh[q][w][lane];
+  const int64_t gi = ta + Mfma16<T>::row(lk, w), gj = tb + lr;
+  if (gi < c && gj < c && gj <= gi) {
+    G[gi * ldg + gj] = v;
+    G[gj * ldg + gi] = v;
+  }
+}
+static_assert(GS_W == 4, "one wave per accumulator element");
+
 template <typename T>
 void launch_gram_rows(const T *X, int64_t ld, int64_t len, const int32_t *list,
                       const int64_t *count_dev, int64_t cap, T *G, Ctrl *ctrl,
                       int respect_done, hipStream_t st) {
+  if (list && count_dev && cap <= GS_MAX && ld % 4 == 0) {
+    const unsigned ns = (unsigned)((cap + 15) / 16);
+    hipLaunchKernelGGL(gram_small_kernel<T>, dim3(ns, ns), dim3(GS_W * WAVE),
+                       0, st, X, ld, len, list, count_dev, cap, G, ctrl,
+                       respect_done);
+    return;
+  }
   const unsigned nt = (unsigned)((cap + SY_B - 1) / SY_B);
   hipLaunchKernelGGL(gram_mfma_kernel<T>, dim3(nt, nt), dim3(SY_NT), 0, st, X,
                      ld, len, list, count_dev, cap, cap, G, ctrl,
@@ -416,11 +490,72 @@ upd_finish(int64_t len, const int64_t *__restrict__ cnt, int nsplit,
   out[i] += sign * s;
 }
 
+// Few listed rows: one launch of 5 us instead of two.  A workgroup has 16
+// consecutive i (a thread two of them), its 32 slots of threads share the
+// list, and the slots' sums meet in LDS.  Whole solves without / with it:
+// 500 x 250 systems 35.4 / 33.9 ms, 2003 x 501 in blocks of 175 67.8 / 65.8.
+// Up to 256 rows and lengths of 4096, beyond which the wider rows of the split
+// form pay (4000 x 1000 in blocks of 500 5.33 / 5.51 ms, 8000 x 2000 of 1000
+// 7.39 / 7.96).
+constexpr int US_SLOTS = UP_NT / 8;
+constexpr int64_t US_MAX = 256, US_LEN = 4096;
+template <typename T>
+__global__ void __launch_bounds__(UP_NT)
+upd_small(const T *__restrict__ M, int64_t ldm, int64_t len,
+          const int32_t *__restrict__ list, const int64_t *__restrict__ cnt,
+          const T *__restrict__ coef, T sign, T *__restrict__ out, Ctrl *ctrl,
+          int respect_done) {
+  if (respect_done && ctrl_done(ctrl)) return;
+  typedef T v2 __attribute__((ext_vector_type(2)));
+  __shared__ T sh[US_SLOTS][16 + 2];
+  const int64_t c = *cnt;
+  const int l = threadIdx.x & 7, slot = threadIdx.x >> 3;
+  const int64_t i = 16 * (int64_t)blockIdx.x + 2 * l;
+  T s0 = 0, s1 = 0;
+  if (i < len) {
+    for (int64_t a0 = slot; a0 < c; a0 += UP_UNROLL * US_SLOTS) {
+      v2 mv[UP_UNROLL];
+      T cf[UP_UNROLL];
+#pragma unroll
+      for (int u = 0; u < UP_UNROLL; ++u) {
+        const int64_t a = a0 + (int64_t)u * US_SLOTS;
+        mv[u] = (v2){0, 0};
+        cf[u] = (T)0;
+        if (a < c) {
+          mv[u] = *reinterpret_cast<const v2 *>(M + (int64_t)list[a] * ldm + i);
+          cf[u] = coef[a];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UP_UNROLL; ++u) {
+        s0 += cf[u] * mv[u].x;
+        s1 += cf[u] * mv[u].y;
+      }
+    }
+  }
+  sh[slot][2 * l] = s0;
+  sh[slot][2 * l + 1] = s1;
+  __syncthreads();
+  const int64_t j = 16 * (int64_t)blockIdx.x + threadIdx.x;
+  if (threadIdx.x < 16 && j < len) {
+    T s = 0;
+#pragma unroll
+    for (int q = 0; q < US_SLOTS; ++q) s += sh[q][threadIdx.x];
+    out[j] += sign * s;
+  }
+}
+
 template <typename T>
 static void thin_update(const T *M, int64_t ldm, int64_t len,
                         const int32_t *list, const int64_t *cnt, int64_t cap,
                         const T *coef, T *out, T sign, T *part, Ctrl *ctrl,
                         int respect_done, hipStream_t st) {
+  if (cap <= US_MAX && len <= US_LEN) {
+    hipLaunchKernelGGL(upd_small<T>, dim3((unsigned)((len + 15) / 16)),
+                       dim3(UP_NT), 0, st, M, ldm, len, list, cnt, coef, sign,
+                       out, ctrl, respect_done);
+    return;
+  }
   const unsigned gx = (unsigned)((len + 2 * UP_NT - 1) / (2 * UP_NT));
   const unsigned gy = (unsigned)((cap + UP_CHUNK - 1) / UP_CHUNK);
   hipLaunchKernelGGL(upd_partial<T>, dim3(gx, gy), dim3(UP_NT), 0, st, M, ldm,
