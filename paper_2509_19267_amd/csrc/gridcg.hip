@@ -330,12 +330,16 @@ struct GcEx {
 
 __global__ void __launch_bounds__(256)
 gc_clear_kernel(double *part, int64_t n, unsigned *seq,
-                unsigned long long *team) {
+                unsigned long long *team, int32_t *cmask, int64_t cols,
+                int32_t *rmask, int64_t rows) {
   unsigned long long *x = reinterpret_cast<unsigned long long *>(part);
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) x[i] = GC_EMPTY;
-  if (i < 2) seq[i] = 0;
-  if (i < 4) team[i] = 0;
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = i0; i < n; i += step) x[i] = GC_EMPTY;
+  for (int64_t i = i0; i < cols; i += step) cmask[i] = 0;
+  for (int64_t i = i0; i < rows; i += step) rmask[i] = 0;
+  if (i0 < 2) seq[i0] = 0;
+  if (i0 < 4) team[i0] = 0;
 }
 
 // Two numbers that are gathered together: at agent scope in one access.
@@ -381,14 +385,15 @@ struct GcPairs {
 // is gathered it is formed from the pair (s, p_old), which its owner replaces
 // by (s_new, p) in the phase in which nobody gathers it.
 // ------------------------------------------------------------ columns
-// W: the block's entries by rows (indices: columns of A); At: all columns.
+// W: the block's entries by rows (indices: columns of A); At: all columns;
+// mask: the block's marks that W was copied with, cleared here.
 //   phase 1: q = A_U p;  phase 2: z -= alpha q, s -= alpha A_U^T q
 template <typename T, bool FULL>
 __device__ __forceinline__ void
 gc_col(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
-       const int32_t *__restrict__ U, int c, const T *__restrict__ g,
-       T *__restrict__ z, T *q, T *sp, double *part, unsigned *seq,
-       int max_steps, double tol, Ctrl *ctrl) {
+       const int32_t *__restrict__ U, int c, int32_t *__restrict__ mask,
+       const T *__restrict__ g, T *__restrict__ z, T *q, T *sp, double *part,
+       unsigned *seq, int max_steps, double tol, Ctrl *ctrl) {
   GcEx<FULL> ex;
   ex.init(ctrl, 0, part, seq, team);
   GcProd<T, FULL> pw, pt;
@@ -406,6 +411,7 @@ gc_col(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
           const T h = g[u];
           if (k >= 0) { uk[k] = u; sk[k] = h; pk[k] = (T)0; }
           SP.put(u, h, (T)0);
+          mask[u] = 0;
           rr += (double)h * (double)h;
         });
         pw.own([&](int k, int i) { if (k >= 0) zk[k] = z[i]; });
@@ -467,18 +473,18 @@ gc_col(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
 template <typename T>
 __global__ void __launch_bounds__(GC_NT)
 gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
-              const int64_t *cnt, const T *g, T *z, T *q, T *sp, double *part,
-              unsigned *seq, unsigned long long *team, int max_steps,
-              double tol, Ctrl *ctrl) {
+              const int64_t *cnt, int32_t *mask, const T *g, T *z, T *q,
+              T *sp, double *part, unsigned *seq, unsigned long long *team,
+              int max_steps, double tol, Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
   GcTeam tm;
   if (!tm.join(team, ctrl)) return;
   if (tm.size == (int)gridDim.x)
-    gc_col<T, true>(tm, W, lgw, At, lgt, U, (int)*cnt, g, z, q, sp, part, seq,
-                    max_steps, tol, ctrl);
+    gc_col<T, true>(tm, W, lgw, At, lgt, U, (int)*cnt, mask, g, z, q, sp, part,
+                    seq, max_steps, tol, ctrl);
   else
-    gc_col<T, false>(tm, W, lgw, At, lgt, U, (int)*cnt, g, z, q, sp, part, seq,
-                     max_steps, tol, ctrl);
+    gc_col<T, false>(tm, W, lgw, At, lgt, U, (int)*cnt, mask, g, z, q, sp, part,
+                     seq, max_steps, tol, ctrl);
 }
 
 // ------------------------------------------------------------ rows
@@ -488,9 +494,9 @@ gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
 template <typename T, bool FULL>
 __device__ __forceinline__ void
 gc_row(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
-       const int32_t *__restrict__ J, int c, const T *__restrict__ r,
-       const double *__restrict__ rho, T *__restrict__ x, T *u, T *zp,
-       T *__restrict__ res, T *__restrict__ v, double *part, unsigned *seq,
+       const int32_t *__restrict__ J, int c, int32_t *__restrict__ mask,
+       const T *__restrict__ r, const double *__restrict__ rho,
+       T *__restrict__ x, T *u, T *zp, T *__restrict__ res, T *__restrict__ v, double *part, unsigned *seq,
        int max_steps, double tol, Ctrl *ctrl) {
   GcEx<FULL> ex;
   ex.init(ctrl, 1, part, seq, team);
@@ -519,6 +525,7 @@ gc_row(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
             res[a] = h;
           }
           ZP.put(i, zz, (T)0);
+          mask[i] = 0;
           a0 += (double)h * (double)zz;
           a1 += (double)h * (double)h;
         });
@@ -591,19 +598,19 @@ gc_row(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
 template <typename T>
 __global__ void __launch_bounds__(GC_NT)
 gc_row_kernel(Csr<T> W, int lgw, Csr<T> A, int lga, const int32_t *J,
-              const int64_t *cnt, const T *r, const double *rho, T *x, T *u,
-              T *zp, T *res, T *v, double *part, unsigned *seq,
+              const int64_t *cnt, int32_t *mask, const T *r,
+              const double *rho, T *x, T *u, T *zp, T *res, T *v, double *part, unsigned *seq,
               unsigned long long *team, int max_steps, double tol,
               Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
   GcTeam tm;
   if (!tm.join(team, ctrl)) return;
   if (tm.size == (int)gridDim.x)
-    gc_row<T, true>(tm, W, lgw, A, lga, J, (int)*cnt, r, rho, x, u, zp, res, v,
-                    part, seq, max_steps, tol, ctrl);
+    gc_row<T, true>(tm, W, lgw, A, lga, J, (int)*cnt, mask, r, rho, x, u, zp,
+                    res, v, part, seq, max_steps, tol, ctrl);
   else
-    gc_row<T, false>(tm, W, lgw, A, lga, J, (int)*cnt, r, rho, x, u, zp, res,
-                     v, part, seq, max_steps, tol, ctrl);
+    gc_row<T, false>(tm, W, lgw, A, lga, J, (int)*cnt, mask, r, rho, x, u, zp,
+                     res, v, part, seq, max_steps, tol, ctrl);
 }
 
 // ------------------------------------------------------------ tall rows
@@ -750,30 +757,35 @@ bool grid_cg_takes(const Csr<T> &A, const Csr<T> &At, int ncu) {
          A.rows * A.group <= most && At.rows * At.group <= most;
 }
 template <typename T>
-void launch_grid_clear(GridCg<T> &w, int ncu, hipStream_t st) {
+void launch_grid_clear(GridCg<T> &w, int ncu, int32_t *cmask, int64_t cols,
+                       int32_t *rmask, int64_t rows, hipStream_t st) {
   const int64_t n = 24 * (int64_t)ncu;
-  hipLaunchKernelGGL(gc_clear_kernel, dim3((unsigned)((n + 255) / 256)),
-                     dim3(256), 0, st, w.part, n, w.seq, w.team);
+  const int64_t b = (std::max({n, cols, rows}) + 255) / 256;
+  hipLaunchKernelGGL(gc_clear_kernel, dim3((unsigned)std::min<int64_t>(b, 1024)),
+                     dim3(256), 0, st, w.part, n, w.seq, w.team, cmask, cols,
+                     rmask, rows);
 }
 template <typename T>
 void launch_grid_colproj(const Csr<T> &W, const Csr<T> &At, const int32_t *U,
-                         const int64_t *cnt, int64_t cap, const T *g, T *z,
+                         const int64_t *cnt, int64_t cap, int32_t *mask,
+                         const T *g, T *z,
                          GridCg<T> &w, int ncu, int max_steps, double tol,
                          Ctrl *ctrl, hipStream_t st) {
   const int grid = gc_grid(W.rows * W.group, cap * At.group, ncu);
   hipLaunchKernelGGL(gc_col_kernel<T>, dim3(grid), dim3(GC_NT), 0, st, W,
-                     gc_log2(W.group), At, gc_log2(At.group), U, cnt, g, z,
+                     gc_log2(W.group), At, gc_log2(At.group), U, cnt, mask, g, z,
                      w.q, w.sp, w.part, w.seq, w.team, max_steps, tol, ctrl);
 }
 template <typename T>
 void launch_grid_rowproj(const Csr<T> &W, const Csr<T> &A, const int32_t *J,
-                         const int64_t *cnt, int64_t cap, const T *r,
+                         const int64_t *cnt, int64_t cap, int32_t *mask,
+                         const T *r,
                          const double *rho, T *x, GridCg<T> &w, T *res, T *v,
                          int ncu, int max_steps, double tol, Ctrl *ctrl,
                          hipStream_t st) {
   const int grid = gc_grid(W.rows * W.group, cap * A.group, ncu);
   hipLaunchKernelGGL(gc_row_kernel<T>, dim3(grid), dim3(GC_NT), 0, st, W,
-                     gc_log2(W.group), A, gc_log2(A.group), J, cnt, r, rho, x,
+                     gc_log2(W.group), A, gc_log2(A.group), J, cnt, mask, r, rho, x,
                      w.q, w.sp, res, v, w.part + 12 * ncu,
                      w.seq + 1, w.team + 2, max_steps, tol, ctrl);
 }
@@ -790,16 +802,17 @@ void launch_grid_tall(const Csr<T> &A, const Csr<T> &At, const int32_t *J,
 }
 
 #define INST_GC(T)                                                            \
-  template void launch_grid_clear<T>(GridCg<T> &, int, hipStream_t);          \
+  template void launch_grid_clear<T>(GridCg<T> &, int, int32_t *, int64_t,     \
+                                     int32_t *, int64_t, hipStream_t);        \
   template bool grid_cg_takes<T>(const Csr<T> &, const Csr<T> &, int);        \
   template void launch_grid_colproj<T>(                                       \
       const Csr<T> &, const Csr<T> &, const int32_t *, const int64_t *,       \
-      int64_t, const T *, T *, GridCg<T> &, int, int, double, Ctrl *,         \
-      hipStream_t);                                                           \
+      int64_t, int32_t *, const T *, T *, GridCg<T> &, int, int, double,      \
+      Ctrl *, hipStream_t);                                                   \
   template void launch_grid_rowproj<T>(                                       \
       const Csr<T> &, const Csr<T> &, const int32_t *, const int64_t *,       \
-      int64_t, const T *, const double *, T *, GridCg<T> &, T *, T *, int,    \
-      int, double, Ctrl *, hipStream_t);                                      \
+      int64_t, int32_t *, const T *, const double *, T *, GridCg<T> &, T *,   \
+      T *, int, int, double, Ctrl *, hipStream_t);                                      \
   template void launch_grid_tall<T>(                                          \
       const Csr<T> &, const Csr<T> &, const int32_t *, const int64_t *,       \
       int64_t, const T *, T *, GridCg<T> &, TallWork<T> &, int, int, double,  \

@@ -448,7 +448,7 @@ void launch_balanced_rowproj(const Csr<T> &csr, const Csr<T> &csc,
 template <typename T>
 Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
                          const int64_t *count_dev, int64_t list_cap,
-                         SubWork &w, Ctrl *ctrl, hipStream_t st);
+                         SubWork &w, int unmark, Ctrl *ctrl, hipStream_t st);
 int64_t sub_scan_tiles(int64_t n);
 // long_flag[r] = 1 for the rows of A longer than A.long_limit
 template <typename T>
@@ -486,19 +486,22 @@ struct GridCg {
   unsigned *seq = nullptr;          // exchanges made (columns, rows)
   unsigned long long *team = nullptr;   // workgroups counted in, team size
 };
-// Empties the exchange slots: before the first launch of every solve.
+// Empties the exchange slots, and the block marks in case a solve broke off:
+// before the first launch of every solve.
 template <typename T>
-void launch_grid_clear(GridCg<T> &w, int ncu, hipStream_t st);
+void launch_grid_clear(GridCg<T> &w, int ncu, int32_t *cmask, int64_t cols,
+                       int32_t *rmask, int64_t rows, hipStream_t st);
 template <typename T>
 bool grid_cg_takes(const Csr<T> &A, const Csr<T> &At, int ncu);
 template <typename T>
 void launch_grid_colproj(const Csr<T> &W, const Csr<T> &At, const int32_t *U,
-                         const int64_t *cnt, int64_t cap, const T *g, T *z,
-                         GridCg<T> &w, int ncu, int max_steps, double tol,
+                         const int64_t *cnt, int64_t cap, int32_t *mask,
+                         const T *g, T *z, GridCg<T> &w, int ncu, int max_steps, double tol,
                          Ctrl *ctrl, hipStream_t st);
 template <typename T>
 void launch_grid_rowproj(const Csr<T> &W, const Csr<T> &A, const int32_t *J,
-                         const int64_t *cnt, int64_t cap, const T *r,
+                         const int64_t *cnt, int64_t cap, int32_t *mask,
+                         const T *r,
                          const double *rho, T *x, GridCg<T> &w, T *res, T *v,
                          int ncu, int max_steps, double tol, Ctrl *ctrl,
                          hipStream_t st);

@@ -1911,7 +1911,7 @@ template void launch_mark_long<float>(const Csr<float> &, uint8_t *, hipStream_t
 template <typename T>
 Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
                          const int64_t *count_dev, int64_t list_cap,
-                         SubWork &w, Ctrl *ctrl, hipStream_t st) {
+                         SubWork &w, int unmark, Ctrl *ctrl, hipStream_t st) {
   const unsigned gm = (unsigned)std::min<int64_t>(
       std::max<int64_t>((list_cap + SB_NT - 1) / SB_NT, 1), 1024);
   hipLaunchKernelGGL(sub_mark, dim3(gm), dim3(SB_NT), 0, st, list, count_dev,
@@ -1930,8 +1930,9 @@ Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
       hipLaunchKernelGGL(sub_fill_long<T>, dim3((unsigned)A.nlong), dim3(SB_NT),
                          0, st, A, w.mask, (const int64_t *)nullptr, w.idx,
                          (T *)w.val, w.cnt, ctrl);
-    hipLaunchKernelGGL(sub_mark, dim3(gm), dim3(SB_NT), 0, st, list, count_dev,
-                       w.mask, 0, ctrl);
+    if (unmark)
+      hipLaunchKernelGGL(sub_mark, dim3(gm), dim3(SB_NT), 0, st, list,
+                         count_dev, w.mask, 0, ctrl);
     Csr<T> B = A;
     B.idx = w.idx;
     B.val = (const T *)w.val;
@@ -2114,8 +2115,8 @@ void launch_balanced_rowproj(const Csr<T> &csr, const Csr<T> &csc,
 INST_BAL(double)
 INST_BAL(float)
 
-template Csr<double> launch_sub_matrix<double>(const Csr<double> &, const int32_t *, const int64_t *, int64_t, SubWork &, Ctrl *, hipStream_t);
-template Csr<float> launch_sub_matrix<float>(const Csr<float> &, const int32_t *, const int64_t *, int64_t, SubWork &, Ctrl *, hipStream_t);
+template Csr<double> launch_sub_matrix<double>(const Csr<double> &, const int32_t *, const int64_t *, int64_t, SubWork &, int, Ctrl *, hipStream_t);
+template Csr<float> launch_sub_matrix<float>(const Csr<float> &, const int32_t *, const int64_t *, int64_t, SubWork &, int, Ctrl *, hipStream_t);
 
 // ------------------------------------------------------------ tall row blocks
 // A row block with more rows than A has columns (k_row > n) is in general

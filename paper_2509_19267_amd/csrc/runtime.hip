@@ -726,7 +726,8 @@ void clear_exchange(rgdbek_ctx *h, Engine<T> &e) {
   hipStream_t st = h->st;
   if (e.cgc.xch) launch_pcg_clear<T>(e.cgc, st);
   if (e.cgr.xch) launch_pcg_clear<T>(e.cgr, st);
-  if (e.gcg.part) launch_grid_clear<T>(e.gcg, h->ncu, st);
+  if (e.gcg.part)
+    launch_grid_clear<T>(e.gcg, h->ncu, e.subc.mask, e.n, e.subr.mask, e.m, st);
 }
 
 template <typename T>
@@ -829,15 +830,16 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     ProfScope ps(h, RGDBEK_PROF_COL_SOLVE, 0);
     const Csr<T> wcsr =
         e.subc.idx && !e.bal_c
-            ? launch_sub_matrix<T>(e.csr, e.U, cntU, e.kc, e.subc, c, st)
+            ? launch_sub_matrix<T>(e.csr, e.U, cntU, e.kc, e.subc,
+                                   !e.gcg.q, c, st)
             : e.csr;
     if (e.bal_c)
       launch_balanced_colproj<T>(e.csr, e.csc, e.subc, e.subr, e.subc.mask,
                                  e.U, cntU, e.kc, e.g, e.z, e.scc, maxs, itol,
                                  c, st);
     else if (e.gcg.q)
-      launch_grid_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.gcg,
-                             h->ncu, maxs, itol, c, st);
+      launch_grid_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.subc.mask, e.g,
+                             e.z, e.gcg, h->ncu, maxs, itol, c, st);
     else
       launch_sparse_colproj<T>(wcsr, e.csc, e.U, cntU, e.kc, e.g, e.z, e.scc,
                              maxs, itol, c, 1, st);
@@ -947,15 +949,16 @@ void enqueue_iteration(rgdbek_ctx *h, Engine<T> &e, const IterOpts &o) {
     ProfScope ps(h, RGDBEK_PROF_ROW_SOLVE, 1);
     const Csr<T> wcsc =
         e.subr.idx && !e.bal_r
-            ? launch_sub_matrix<T>(e.csc, e.J, cntJ, e.kr, e.subr, c, st)
+            ? launch_sub_matrix<T>(e.csc, e.J, cntJ, e.kr, e.subr,
+                                   !e.gcg.q, c, st)
             : e.csc;
     if (e.bal_r)
       launch_balanced_rowproj<T>(e.csr, e.csc, e.subc, e.subr, e.subr.mask,
                                  e.J, cntJ, e.kr, e.r, e.rho, e.x, e.scr, maxs,
                                  itol, c, st);
     else if (e.gcg.q)
-      launch_grid_rowproj<T>(wcsc, e.csr, e.J, cntJ, e.kr, e.r, e.rho, e.x,
-                             e.gcg, e.scr.res, e.scr.v, h->ncu, maxs, itol, c,
+      launch_grid_rowproj<T>(wcsc, e.csr, e.J, cntJ, e.kr, e.subr.mask, e.r,
+                             e.rho, e.x, e.gcg, e.scr.res, e.scr.v, h->ncu, maxs, itol, c,
                              st);
     else
       launch_sparse_rowproj<T>(e.csr, wcsc, e.J, cntJ, e.kr, e.r, e.rho, e.x,
