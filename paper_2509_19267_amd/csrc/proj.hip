@@ -7,13 +7,14 @@
 // d = A^J^T w with (A^J A^J^T) w = r^J.
 //
 // Dense blocks: Gram matrix (gathered from a precomputed A^T A / A A^T, or
-// formed from the listed rows), then a one-workgroup blocked Cholesky with an
-// optional corrected semi-normal-equations sweep (ill-conditioned square row
-// blocks), or Jacobi-preconditioned CG with one launch per step (the last
-// workgroup of each step carries the vector recurrences).
+// formed from the listed rows), then a Cholesky in one workgroup (chol.hip)
+// with an optional corrected semi-normal-equations sweep (ill-conditioned
+// square row blocks), or Jacobi-preconditioned CG: in one persistent launch
+// (pcg.hip) or, for blocks that do not fit the device, two launches a step.
 // Sparse blocks: matrix-free CGLS (columns, z updated as the CGLS residual)
-// and CGNE on A^J A^J^T (rows), the wide products streaming the full CSR/CSC
-// with a direction vector that is zero outside the block.
+// and CGNE on A^J A^J^T (rows), over copies of the block's entries: in one
+// launch (gridcg.hip), with products balanced by nonzeros (balprod.hip) or
+// with a fixed number of lanes per row.
 #include <algorithm>
 
 #include "common.h"
