@@ -409,9 +409,9 @@ def profiled_solve(prob, form, choice, tol, stream, dev):
 
 def solve_roofline(prof, form, choice, m, n):
     """Roofline entry of the dominant region of a dense solve.  The block
-    solves run one persistent PCG launch per projection; its algorithmic
-    bytes are one read of the k x k Gram block per CG step (steps from the
-    profile's step counts)."""
+    solves run one persistent PCG launch per projection, which keeps the
+    k x k Gram block on the chip for all its steps; its algorithmic bytes are
+    one read of the block."""
     vb = 4 if form == "mixed_f32" else 8
     best = max((r for r in prof if r != "refine"), key=lambda r: prof[r]["ms"])
     reg = prof[best]
@@ -421,7 +421,7 @@ def solve_roofline(prof, form, choice, m, n):
     if best in ("col_solve", "row_solve"):
         k = choice["k_col"] if best == "col_solve" else choice["k_row"]
         steps = reg["steps"] / n_l
-        alg = steps * k * k * vb
+        alg = k * k * vb
         out.update(kernel=f"pcg_persist_kernel<{'float' if vb == 4 else 'double'}>"
                           f" ({'column' if best == 'col_solve' else 'row'} block, k = {k})",
                    cg_steps_per_launch=round(steps, 2), alg_bytes_per_launch=int(alg))
