@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "mergeplan.h"
 
 namespace rg {
 
@@ -217,8 +218,7 @@ struct SegArgs {
 template <typename T>
 int launch_segdot(const Csr<T> &A, int epi, const SegArgs<T> &a, Ctrl *ctrl,
                   int respect_done, hipStream_t st);   // returns #partials
-// nonzeros per merge chunk (one wave); partial slots a full pass may use
-constexpr int64_t MP_CH = 256;
+// partial slots a full pass may use
 int64_t segdot_max_parts(int64_t rows, int64_t nnz, int64_t nchunk,
                          int64_t ncross, int64_t nlong, int64_t rep);
 

@@ -1452,36 +1452,16 @@ void build_longs(rgdbek_ctx *h, const int64_t *ptr_dev, int64_t rows,
                      hipMemcpyHostToDevice));
 }
 
-// Chunk c holds nonzeros [c*MP_CH, (c+1)*MP_CH); it owns the rows whose
-// first nonzero position lies in it (empty rows: the position of the next
-// nonzero; trailing empty rows: the last chunk).  Rows running past their
-// chunk are listed with their first and last chunk.
+// The nonzero-balanced plan of a residual pass (mergeplan.h) on the device.
 void build_merge_plan(rgdbek_ctx *h, const int64_t *ptr_dev, int64_t rows,
                       MergePlan *mp) {
   std::vector<int64_t> rp(rows + 1);
   HIPCHK(hipMemcpy(rp.data(), ptr_dev, sizeof(int64_t) * (rows + 1),
                    hipMemcpyDeviceToHost));
-  const int64_t nnz = rp[rows];
-  const int64_t nch = std::max<int64_t>(1, (nnz + MP_CH - 1) / MP_CH);
-  std::vector<int32_t> rs(nch + 1);
-  for (int64_t c = 0; c < nch; ++c)
-    rs[c] = (int32_t)(std::lower_bound(rp.begin(), rp.begin() + rows,
-                                       c * MP_CH) - rp.begin());
-  rs[nch] = (int32_t)rows;
-  std::vector<int32_t> xr, xs, xe;
-  for (int64_t r = 0; r < rows; ++r) {
-    if (rp[r + 1] == rp[r]) continue;
-    const int64_t cs = rp[r] / MP_CH, ce = (rp[r + 1] - 1) / MP_CH;
-    if (ce > cs) {
-      xr.push_back((int32_t)r);
-      xs.push_back((int32_t)cs);
-      xe.push_back((int32_t)ce);
-    }
-  }
-  mp->nchunk = nch;
-  for (int64_t c = 0; c < nch; ++c)
-    mp->maxrows = std::max<int64_t>(mp->maxrows, rs[c + 1] - rs[c]);
-  mp->ncross = (int64_t)xr.size();
+  const MergeRows p = merge_rows(rp.data(), rows);
+  mp->nchunk = p.nchunk;
+  mp->maxrows = p.maxrows;
+  mp->ncross = (int64_t)p.xrow.size();
   auto up = [&](const std::vector<int32_t> &v) {
     int32_t *d = h->pool.alloc<int32_t>(std::max<int64_t>(1, (int64_t)v.size()), false);
     if (!v.empty())
@@ -1489,10 +1469,10 @@ void build_merge_plan(rgdbek_ctx *h, const int64_t *ptr_dev, int64_t rows,
                        hipMemcpyHostToDevice));
     return d;
   };
-  mp->rs = up(rs);
-  mp->xrow = up(xr);
-  mp->xcs = up(xs);
-  mp->xce = up(xe);
+  mp->rs = up(p.rs);
+  mp->xrow = up(p.xrow);
+  mp->xcs = up(p.xcs);
+  mp->xce = up(p.xce);
 }
 
 void create_impl(rgdbek_ctx *h, const rgdbek_matrix *A) {

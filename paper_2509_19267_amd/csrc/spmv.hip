@@ -150,7 +150,7 @@ mp_chunks(Csr<T> A, SegArgs<T> a, Ctrl *ctrl, int respect_done) {
     const int64_t eb = e0 + (int64_t)lane * MP_K;
     const int64_t rs = A.mp_rs[c], re = A.mp_rs[c + 1];
     // the lane's first owned row, loaded beside the gathers
-    const int64_t rf = rs + lane < re ? rs + lane : rs;
+    const int64_t rf = mp_first_row(rs, re, lane, A.rows);
     int64_t f0, f1, pe = 0;
     T pv[MP_K];
     if (eh == e0 + MP_CH) {
