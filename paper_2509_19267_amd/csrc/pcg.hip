@@ -26,8 +26,10 @@
 // Three exchange buffers rotate: a workgroup that has read all of step s
 // knows that everybody has finished reading step s - 1, and clears its share
 // of that buffer then; the clear has landed (vmcnt wait) before the same
-// wave publishes step s + 1, without which nobody reads step s + 2.  The
-// rotation goes on across launches (seq).  Polls are bounded: a timed-out
+// wave publishes step s + 1, without which nobody reads step s + 2.  That
+// holds because every workgroup that reads also publishes: those without a
+// row leave at once (pcgshare.h).  The rotation goes on across launches
+// (seq, read before the first publish and written after the last).  Polls are bounded: a timed-out
 // wait raises Ctrl::sync_fail, which ends the other waits, so the launch
 // always drains.
 // Measured per launch, against the same CG with the block re-read from
@@ -38,6 +40,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "lanes.h"
+#include "pcgshare.h"
 
 namespace rg {
 
@@ -104,8 +107,9 @@ pcg_persist_kernel(const PqArgs<T> a) {
   __shared__ int s_fail;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
   const int c = (int)*a.cnt;
-  const int P = (int)gridDim.x;
-  const int rpw = (c + P - 1) / P;
+  const PqShare share = pq_share(c, a.cap, (int)gridDim.x);
+  if ((int)blockIdx.x >= share.active) return;
+  const int rpw = share.rpw;
   const int r0 = (int)blockIdx.x * rpw;
   const int nr = c - r0 < rpw ? (c - r0 > 0 ? c - r0 : 0) : rpw;
   const int ph = a.ph;
@@ -306,10 +310,9 @@ pcg_persist_kernel(const PqArgs<T> a) {
     // everybody has read the previous step: clear this workgroup's share
     if (wv == 0) {
       B *xp = reinterpret_cast<B *>(a.xch) + (int64_t)((s + 2) % 3) * a.cap;
-      const int per = (a.cap + P - 1) / P;
-      const int i1 = ((int)blockIdx.x + 1) * per < a.cap
-                         ? ((int)blockIdx.x + 1) * per : a.cap;
-      for (int i = (int)blockIdx.x * per + lane; i < i1; i += WAVE)
+      const int i0 = (int)blockIdx.x * share.per;
+      const int i1 = i0 + share.per < a.cap ? i0 + share.per : a.cap;
+      for (int i = i0 + lane; i < i1; i += WAVE)
         st_agent(&xp[i], EMPTY);
     }
     pv = 0.0;
