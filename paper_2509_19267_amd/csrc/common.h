@@ -46,7 +46,7 @@ struct Ctrl {
   uint64_t sel_bar[2];    // grid-barrier arrivals of the persistent selection
   uint64_t sel_barbase[2];
   int32_t sync_fail;      // a wait between workgroups timed out
-  int32_t pad0;
+  int32_t team_max;       // cap on a launch's team (team.h); 0: none
   unsigned ticket[8];     // last-block tickets (reset by the last block)
 };
 

@@ -24,6 +24,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "lanes.h"
+#include "team.h"
 
 namespace rg {
 
@@ -32,7 +33,6 @@ constexpr int GC_NODE = 64;
 constexpr int GC_KEEP = 2;     // segments of a lane group kept in registers
 constexpr int GC_ENT = 3;      // entries of each kept in registers by a lane
 constexpr unsigned long long GC_EMPTY = 0x7FF4A5C35A3C1E87ull;
-constexpr long long GC_WAIT = 20000;   // 200 us, see GcTeam
 constexpr int GC_SEGS = 8;     // segments per lane group a block may have
 
 template <typename T>
@@ -146,51 +146,9 @@ struct GcProd {
   }
 };
 
-// The workgroups that are on the device together.  Nothing says that all of a
-// launch are: another stream's launch of this kind may hold the other half of
-// the compute units and wait as well.  So every workgroup counts itself in;
-// the first one waits a moment (GC_WAIT of the 100 MHz clock) for the others
-// and fixes the number; who comes later leaves at once.  The shares of those
-// are taken by the ones that are there (share b of rank b mod size), with the
-// same sums in the same order, so that the results do not depend on it.
-// Counts go on over a solve's launches: each adds the whole grid.
-struct GcTeam {
-  int rank, size;
-  // false for a workgroup that came too late
-  __device__ __forceinline__ bool join(unsigned long long *tm, Ctrl *ctrl) {
-    __shared__ int s_rank, s_size;
-    if (threadIdx.x == 0) {
-      const unsigned long long V = gridDim.x;
-      const unsigned long long old = __hip_atomic_fetch_add(
-          &tm[0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long launch = old / V;
-      const unsigned long long tag = launch + 1;
-      unsigned long long n = 0;
-      s_rank = (int)(old % V);
-      if (old % V == 0) {
-        const long long t0 = wall_clock64();
-        do n = ld_agent(&tm[0]) - launch * V;
-        while (n < V && wall_clock64() - t0 < GC_WAIT);
-        st_agent(&tm[1], tag << 16 | n);
-      } else {
-        int64_t spins = 0;
-        while (((n = ld_agent(&tm[1])) >> 16) != tag) {
-          if (++spins > GRID_SPIN_MAX) {
-            st_agent(&ctrl->sync_fail, 1);
-            n = 0;
-            break;
-          }
-        }
-        n &= 0xffff;
-      }
-      s_size = (int)n;
-    }
-    __syncthreads();
-    rank = s_rank;
-    size = s_size;
-    return rank < size;
-  }
-};
+// The workgroups that are on the device together (team.h) take the shares of
+// those that are not (share b of rank b mod size), with the same sums in the
+// same order, so that the results do not depend on it.
 
 // What the workgroups exchange between two phases: two partial sums per
 // share, which are also the barrier.  A workgroup publishes its own once all
@@ -208,10 +166,10 @@ struct GcEx {
   unsigned *seqp;
   unsigned seq;
   int ph;
-  GcTeam tm;
+  Team tm;
 
   __device__ __forceinline__ void init(Ctrl *ctrl, int phase, double *part,
-                                       unsigned *sq, const GcTeam &team) {
+                                       unsigned *sq, const Team &team) {
     c = ctrl;
     ph = phase;
     slots = reinterpret_cast<unsigned long long *>(part);
@@ -390,7 +348,7 @@ struct GcPairs {
 //   phase 1: q = A_U p;  phase 2: z -= alpha q, s -= alpha A_U^T q
 template <typename T, bool FULL>
 __device__ __forceinline__ void
-gc_col(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
+gc_col(const Team &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
        const int32_t *__restrict__ U, int c, int32_t *__restrict__ mask,
        const T *__restrict__ g, T *__restrict__ z, T *q, T *sp, double *part,
        unsigned *seq, int max_steps, double tol, Ctrl *ctrl) {
@@ -477,8 +435,9 @@ gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
               T *sp, double *part, unsigned *seq, unsigned long long *team,
               int max_steps, double tol, Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
-  GcTeam tm;
-  if (!tm.join(team, ctrl)) return;
+  Team tm;
+  tm.enter(team);
+  if (!tm.settle(team, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_col<T, true>(tm, W, lgw, At, lgt, U, (int)*cnt, mask, g, z, q, sp, part,
                     seq, max_steps, tol, ctrl);
@@ -493,7 +452,7 @@ gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
 //   phase 3: x += alpha u, res -= alpha v, zz = res / rho
 template <typename T, bool FULL>
 __device__ __forceinline__ void
-gc_row(const GcTeam &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
+gc_row(const Team &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
        const int32_t *__restrict__ J, int c, int32_t *__restrict__ mask,
        const T *__restrict__ r, const double *__restrict__ rho,
        T *__restrict__ x, T *u, T *zp, T *__restrict__ res, T *__restrict__ v, double *part, unsigned *seq,
@@ -603,8 +562,9 @@ gc_row_kernel(Csr<T> W, int lgw, Csr<T> A, int lga, const int32_t *J,
               unsigned long long *team, int max_steps, double tol,
               Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
-  GcTeam tm;
-  if (!tm.join(team, ctrl)) return;
+  Team tm;
+  tm.enter(team);
+  if (!tm.settle(team, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_row<T, true>(tm, W, lgw, A, lga, J, (int)*cnt, mask, r, rho, x, u, zp,
                     res, v, part, seq, max_steps, tol, ctrl);
@@ -619,7 +579,7 @@ gc_row_kernel(Csr<T> W, int lgw, Csr<T> A, int lga, const int32_t *J,
 //   phase 1: q = A^J p;  phase 2: d += alpha p, s = A^T (r - alpha q)
 template <typename T, bool FULL>
 __device__ __forceinline__ void
-gc_tall(const GcTeam &team, const Csr<T> &A, int lga, const Csr<T> &At,
+gc_tall(const Team &team, const Csr<T> &A, int lga, const Csr<T> &At,
         int lgt, const int32_t *__restrict__ J, int c,
         const T *__restrict__ r, T *__restrict__ x, T *__restrict__ d, T *rq,
         T *sp, double *part, unsigned *seq, int max_steps, double tol,
@@ -723,8 +683,9 @@ gc_tall_kernel(Csr<T> A, int lga, Csr<T> At, int lgt, const int32_t *J,
                double *part, unsigned *seq, unsigned long long *team,
                int max_steps, double tol, Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
-  GcTeam tm;
-  if (!tm.join(team, ctrl)) return;
+  Team tm;
+  tm.enter(team);
+  if (!tm.settle(team, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_tall<T, true>(tm, A, lga, At, lgt, J, (int)*cnt, r, x, d, rq, sp, part,
                      seq, max_steps, tol, ctrl);

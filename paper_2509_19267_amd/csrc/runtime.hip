@@ -139,6 +139,7 @@ struct rgdbek_ctx {
   rgdbek_params p{};
   int64_t kc = 0, kr = 0;
   int ncu = 256;                  // compute units of the device
+  int team_max = 0;               // Ctrl::team_max of the solves
   hipStream_t user_st = nullptr;  // caller's stream (inputs are ordered on it)
   hipStream_t st = nullptr;       // the stream all work is enqueued on
   bool own_stream = false;        // st was created by the handle
@@ -1014,6 +1015,7 @@ void ctrl_reset(rgdbek_ctx *h, int64_t it0, int64_t max_iter, int stop,
   c.stop_mode = stop;
   c.tol = tol;
   c.done = max_iter <= 0 ? 1 : 0;
+  c.team_max = h->team_max;
   HIPCHK(hipMemcpyAsync(h->ctrl, &c, sizeof(Ctrl), hipMemcpyHostToDevice,
                         h->st));
 }
@@ -2360,6 +2362,14 @@ rgdbek_status rgdbek_profile_read(rgdbek_handle h, int32_t region,
   if (launches) *launches = r.launches;
   if (ms) *ms = r.ms;
   if (steps) *steps = r.steps;
+  return RGDBEK_OK;
+}
+
+// For tests, not part of the API: at most n workgroups of a launch stay (see
+// team.h; 0: no limit) in the solves that follow.
+rgdbek_status rgdbek_debug_team_limit(rgdbek_handle h, int32_t n) {
+  if (!h || n < 0) return RGDBEK_ERR_INVALID_ARG;
+  h->team_max = n;
   return RGDBEK_OK;
 }
 
