@@ -436,8 +436,9 @@ gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
               int max_steps, double tol, Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
   Team tm;
-  tm.enter(team);
-  if (!tm.settle(team, ctrl)) return;
+  __shared__ unsigned long long s_old;
+  tm.enter(team, &s_old);
+  if (!tm.settle(team, &s_old, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_col<T, true>(tm, W, lgw, At, lgt, U, (int)*cnt, mask, g, z, q, sp, part,
                     seq, max_steps, tol, ctrl);
@@ -563,8 +564,9 @@ gc_row_kernel(Csr<T> W, int lgw, Csr<T> A, int lga, const int32_t *J,
               Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
   Team tm;
-  tm.enter(team);
-  if (!tm.settle(team, ctrl)) return;
+  __shared__ unsigned long long s_old;
+  tm.enter(team, &s_old);
+  if (!tm.settle(team, &s_old, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_row<T, true>(tm, W, lgw, A, lga, J, (int)*cnt, mask, r, rho, x, u, zp,
                     res, v, part, seq, max_steps, tol, ctrl);
@@ -684,8 +686,9 @@ gc_tall_kernel(Csr<T> A, int lga, Csr<T> At, int lgt, const int32_t *J,
                int max_steps, double tol, Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
   Team tm;
-  tm.enter(team);
-  if (!tm.settle(team, ctrl)) return;
+  __shared__ unsigned long long s_old;
+  tm.enter(team, &s_old);
+  if (!tm.settle(team, &s_old, ctrl)) return;
   if (tm.size == (int)gridDim.x)
     gc_tall<T, true>(tm, A, lga, At, lgt, J, (int)*cnt, r, x, d, rq, sp, part,
                      seq, max_steps, tol, ctrl);

@@ -300,6 +300,7 @@ struct CgWork {
   double *rzs = nullptr;     // rz by step parity (2)
   T *xch = nullptr;          // persistent PCG: G p, three buffers (3 * cap)
   unsigned *seq = nullptr;   // persistent PCG: steps since they were cleared
+  unsigned long long *team = nullptr;   // and its workgroups (team.h)
 };
 // Persistent PCG (one launch per projection, pcg.hip): whether a block
 // capacity fits it, and its grid.

@@ -2,6 +2,10 @@
 // whole CG of one block projection (Section 2's pseudoinverse updates) in
 // one launch of at most one workgroup per compute unit.
 //
+// The workgroups need not all be on the device: those that are (team.h) deal
+// the block's rows among themselves, with the same bits whatever their number
+// (fewer hold more rows, streamed from G where registers and LDS are full).
+// Counting them costs 2-3 us a launch: 2003 x 501 layer 43.5 -> 45.1 ms.
 // Workgroup w owns rows [w rpw, (w+1) rpw) of the block G; thread t of every
 // workgroup owns columns t, t + 512, ... of it.  What bounds a CG step is
 // not the product but the exchange between the workgroups, and reading the
@@ -41,6 +45,7 @@
 #include "kernels.h"
 #include "lanes.h"
 #include "pcgshare.h"
+#include "team.h"
 
 namespace rg {
 
@@ -74,6 +79,7 @@ struct PqArgs {
   T *y;
   T *xch;               // 3 x cap exchange buffers
   unsigned *seq;        // steps exchanged since the buffers were cleared
+  unsigned long long *team;   // workgroups counted in, team size
   int cap, max_steps;
   double tol;
   Ctrl *ctrl;
@@ -107,13 +113,10 @@ pcg_persist_kernel(const PqArgs<T> a) {
   __shared__ int s_fail;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
   const int c = (int)*a.cnt;
-  const PqShare share = pq_share(c, a.cap, (int)gridDim.x);
-  if ((int)blockIdx.x >= share.active) return;
-  const int rpw = share.rpw;
-  const int r0 = (int)blockIdx.x * rpw;
-  const int nr = c - r0 < rpw ? (c - r0 > 0 ? c - r0 : 0) : rpw;
+  Team team;
+  __shared__ unsigned long long s_old;
+  int me, per, r0, nr;
   const int ph = a.ph;
-  const unsigned seq = *a.seq;
   if (tid == 0) s_fail = 0;
   for (int k = tid; k < PQ_RMAX; k += PQ_NT) ys[k] = (T)0;
 
@@ -129,6 +132,7 @@ pcg_persist_kernel(const PqArgs<T> a) {
       const int col = tid + j * PQ_NT;
       off[j] = col < c ? a.hl[col] : 0;
     }
+    team.enter(a.team, &s_old);
     T d[NC];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
@@ -144,6 +148,15 @@ pcg_persist_kernel(const PqArgs<T> a) {
       return a.F ? a.F + (int64_t)a.hl[r0 + k] * a.ldf
                  : a.G + (int64_t)(r0 + k) * a.ldg;
     };
+    // who is there, and this workgroup's share
+    if (!team.settle(a.team, &s_old, ctrl, (a.cap + PQ_RMAX - 1) / PQ_RMAX))
+      return;
+    const PqShare share = pq_share(c, a.cap, team.size);
+    me = team.size == (int)gridDim.x ? (int)blockIdx.x : team.rank;
+    per = share.per;
+    if (me >= share.active) return;
+    r0 = me * share.rpw;
+    nr = c - r0 < share.rpw ? (c - r0 > 0 ? c - r0 : 0) : share.rpw;
 #pragma unroll
     for (int k = 0; k < RR; ++k) {
       if (k < nr) {
@@ -198,6 +211,7 @@ pcg_persist_kernel(const PqArgs<T> a) {
 #pragma unroll
   for (int w = 0; w < PQ_NW; ++w) { rz += sh[1][w]; rr += sh[2][w]; }
   const double rr0 = rr;
+  const unsigned seq = ld_agent(a.seq);
   __syncthreads();   // sh[1], sh[2] are written again in the first step
 
   int t = 0;
@@ -310,8 +324,8 @@ pcg_persist_kernel(const PqArgs<T> a) {
     // everybody has read the previous step: clear this workgroup's share
     if (wv == 0) {
       B *xp = reinterpret_cast<B *>(a.xch) + (int64_t)((s + 2) % 3) * a.cap;
-      const int i0 = (int)blockIdx.x * share.per;
-      const int i1 = i0 + share.per < a.cap ? i0 + share.per : a.cap;
+      const int i0 = me * per;
+      const int i1 = i0 + per < a.cap ? i0 + per : a.cap;
       for (int i = i0 + lane; i < i1; i += WAVE)
         st_agent(&xp[i], EMPTY);
     }
@@ -346,7 +360,7 @@ pcg_persist_kernel(const PqArgs<T> a) {
   }
   __syncthreads();
   for (int k = tid; k < nr; k += PQ_NT) a.y[r0 + k] = ys[k];
-  if (blockIdx.x == 0 && tid == 0) {
+  if (me == 0 && tid == 0) {
     *a.seq = seq + (unsigned)t;
     ctrl->cg_steps[ph] = t;
     ctrl->cg_done[ph] = 1;
@@ -355,12 +369,13 @@ pcg_persist_kernel(const PqArgs<T> a) {
 
 template <typename T>
 __global__ void __launch_bounds__(256)
-pcg_clear_kernel(T *xch, int64_t n, unsigned *seq) {
+pcg_clear_kernel(T *xch, int64_t n, unsigned *seq, unsigned long long *team) {
   using B = typename PqBits<T>::type;
   B *x = reinterpret_cast<B *>(xch);
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) x[i] = PqBits<T>::empty;
   if (i == 0) *seq = 0;
+  if (i < 2) team[i] = 0;
 }
 
 static int64_t pcg_persist_cap(bool f64) { return f64 ? 4096 : 8192; }
@@ -381,7 +396,7 @@ template <typename T>
 void launch_pcg_clear(CgWork<T> &w, hipStream_t st) {
   const int64_t n = 3 * w.cap;
   hipLaunchKernelGGL(pcg_clear_kernel<T>, dim3((unsigned)((n + 255) / 256)),
-                     dim3(256), 0, st, w.xch, n, w.seq);
+                     dim3(256), 0, st, w.xch, n, w.seq, w.team);
 }
 
 template <typename T>
@@ -396,7 +411,7 @@ void launch_pcg_persist(T *G, int64_t cap, const int64_t *count_dev,
   hipLaunchKernelGGL((pcg_persist_kernel<T, NC, RR, RL>), dim3(grid),        \
                      dim3(PQ_NT), 0, st,                                     \
                      (PqArgs<T>{G, F, cap, ldf, count_dev, hsrc, hlist,  \
-                                    nrm, y, w.xch, w.seq, (int)cap,          \
+                                    nrm, y, w.xch, w.seq, w.team, (int)cap,  \
                                     max_steps, tol, ctrl, ph}))
   if (cap <= 1 * PQ_NT) RG_PQ(1, 16, 0);
   else if (cap <= 2 * PQ_NT) RG_PQ(2, 16, 0);

@@ -249,6 +249,7 @@ void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e) {
     cw->rzs = P.alloc<double>(2);
     cw->xch = P.alloc<T>(3 * cap, false);
     cw->seq = P.alloc<unsigned>(1);
+    cw->team = P.alloc<unsigned long long>(2);
   }
 }
 

@@ -1,4 +1,5 @@
-// The workgroups of a launch that are on the device together (gridcg.hip).
+// The workgroups of a launch that are on the device together (gridcg.hip,
+// pcg.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -13,33 +14,45 @@ namespace rg {
 // comes later leaves.  The shares of those are taken by the ones that are
 // there.  Counts go on over a solve's launches: each adds the whole grid.
 // Ctrl::team_max (0: none) caps the number, so that a test can have every
-// size of team: the workgroups above it leave as late ones do.
+// size of team: the workgroups above it leave as late ones do.  A kernel that
+// needs at least `least` of them waits for those (bounded, Ctrl::sync_fail).
 constexpr long long TEAM_WAIT = 20000;   // 200 us
 struct Team {
-  unsigned long long old;   // thread 0: workgroups counted in before this one
   int rank, size;
 
-  __device__ __forceinline__ void enter(unsigned long long *tm) {
+  // s_old: workgroups counted in before this one (thread 0's)
+  __device__ __forceinline__ void enter(unsigned long long *tm,
+                                        unsigned long long *s_old) {
     if (threadIdx.x == 0)
-      old = __hip_atomic_fetch_add(&tm[0], 1ull, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+      *s_old = __hip_atomic_fetch_add(&tm[0], 1ull, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
   }
   // false for a workgroup that came too late
-  __device__ __forceinline__ bool settle(unsigned long long *tm, Ctrl *ctrl) {
+  __device__ __forceinline__ bool settle(unsigned long long *tm,
+                                         const unsigned long long *s_old,
+                                         Ctrl *ctrl, int least = 1) {
     __shared__ int s_rank, s_size;
     if (threadIdx.x == 0) {
-      const unsigned long long V = gridDim.x;
+      const unsigned long long V = gridDim.x, old = *s_old;
       const unsigned long long launch = old / V;
       const unsigned long long tag = launch + 1;
       unsigned long long n = 0;
       s_rank = (int)(old % V);
       if (old % V == 0) {
         const unsigned long long cap = (unsigned long long)ctrl->team_max;
-        const unsigned long long want = cap > 0 && cap < V ? cap : V;
+        unsigned long long want = cap > 0 && cap < V ? cap : V;
+        if (want < (unsigned long long)least) want = least;
         const long long t0 = wall_clock64();
+        int64_t spins = 0;
         do n = ld_agent(&tm[0]) - launch * V;
-        while (n < want && wall_clock64() - t0 < TEAM_WAIT);
+        while (n < want && (wall_clock64() - t0 < TEAM_WAIT ||
+                            (n < (unsigned long long)least &&
+                             ++spins <= GRID_SPIN_MAX)));
         if (n > want) n = want;
+        if (n < (unsigned long long)least) {
+          st_agent(&ctrl->sync_fail, 1);
+          n = 0;
+        }
         st_agent(&tm[1], tag << 16 | n);
       } else {
         int64_t spins = 0;
@@ -55,8 +68,8 @@ struct Team {
       s_size = (int)n;
     }
     __syncthreads();
-    rank = s_rank;
-    size = s_size;
+    rank = __builtin_amdgcn_readfirstlane(s_rank);
+    size = __builtin_amdgcn_readfirstlane(s_size);
     return rank < size;
   }
 };
