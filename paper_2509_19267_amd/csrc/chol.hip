@@ -27,6 +27,7 @@
 // Larger blocks (on request) keep L in global memory, over G: the other
 // waves form panel p + 1 from the panels before p, read back through L2,
 // while wave 0 factors panel p.
+#include <limits>
 #include <utility>
 
 #include "common.h"
@@ -63,8 +64,8 @@ __device__ __forceinline__ void tile_put(const typename Mfma16<T>::v4 &v, T *t) 
     t[Mfma16<T>::row(lane >> 4, u) * CH_P + (lane & 15)] = v[u];
 }
 
-// 1 / d to the last bits for a normal d: the hardware estimate (24 bits)
-// with a third-order correction.
+// 1 / d to the last bits for a normal d with a normal reciprocal: the hardware
+// estimate (24 bits) with a third-order correction.
 __device__ __forceinline__ double recip(double d) {
   const double r = __builtin_amdgcn_rcp(d);
   const double e = fma(-d, r, 1.0);
@@ -157,9 +158,22 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
   for (int e = tid; e < CH_B * CH_P; e += CR_NT) zero[e] = (T)0;
   T *wi = W + CR_TILES;
   T thr = (T)0;
+  // The block is factored as sc G, sc a power of 4 that takes its largest
+  // diagonal entry near 1 (denormal ones to 2^-25), so that the pivots above
+  // the threshold and their reciprocals are normal numbers (exact: the same
+  // bits as without).
+  T sc = (T)1;
   if (factor) {
-    thr = diag_max<CR_NT, T>(G, ldg, c, wmax) * (T)1e-13;
+    const T mx = diag_max<CR_NT, T>(G, ldg, c, wmax);
+    int ex = 0;
+    if (mx > (T)0 && mx <= std::numeric_limits<T>::max()) (void)frexp(mx, &ex);
+    constexpr int lim = std::numeric_limits<T>::max_exponent - 4;
+    ex = (ex < -lim ? -lim : ex > lim ? lim : ex) & ~1;
+    sc = ldexp((T)1, -ex);
+    thr = mx * sc * (T)1e-13;
+    if (tid == 0) wi[CR_MAX * CH_B] = sc;
   } else {
+    sc = wi[CR_MAX * CH_B];
     for (int e = tid; e < nt * CH_B * CH_B; e += CR_NT)
       li[e / (CH_B * CH_B)][e / CH_B % CH_B * CH_P + e % CH_B] = wi[e];
   }
@@ -246,6 +260,9 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
           acc[s][u] = i < c && k < c ? g : (T)0;
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < CR_OWN; ++s) acc[s] *= sc;
 #pragma unroll
       for (int s = 0; s < CR_OWN; ++s)
         if (tj[s] == 0) tile_put<T>(acc[s], &pan[0][ti[s] * CH_B * CH_P]);
@@ -337,7 +354,7 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
       __syncthreads();
     }
   }
-  if (tid < c) y[tid] = ys[tid];
+  if (tid < c) y[tid] = ys[tid] * sc;
 }
 
 // ------------------------------------------------------------ up to CHOL_MAX
@@ -546,7 +563,7 @@ chol_big_kernel(T *__restrict__ G, int64_t ldg,
 }
 
 int64_t chol_work_size(int64_t cap) {
-  return cap <= CR_MAX ? CR_TILES + CR_MAX * CH_B : 1;
+  return cap <= CR_MAX ? CR_TILES + CR_MAX * CH_B + 1 : 1;
 }
 
 template <typename T>
