@@ -301,6 +301,7 @@ struct CgWork {
   T *xch = nullptr;          // persistent PCG: G p, three buffers (3 * cap)
   unsigned *seq = nullptr;   // persistent PCG: steps since they were cleared
   unsigned long long *team = nullptr;   // and its workgroups (team.h)
+  bool divide = false;       // norms without a reciprocal: not persistent
 };
 // Persistent PCG (one launch per projection, pcg.hip): whether a block
 // capacity fits it, and its grid.
@@ -530,6 +531,8 @@ void launch_sqnorms_csr(const Csr<T> &A, double *out, hipStream_t st);
 // flag[0] |= any non-finite among n values
 template <typename T>
 void launch_check_finite(const T *v, int64_t n, int *flag, hipStream_t st);
+// *flag |= 1 (2): a norm that is not zero has no normal FP64 (FP32) reciprocal
+void launch_recip_range(const double *v, int64_t n, int *flag, hipStream_t st);
 // CSR -> CSC transpose on the device (stable: rows ascending in a column)
 template <typename T>
 void launch_csr_to_csc(int64_t m, int64_t n, int64_t nnz, const int64_t *rp,

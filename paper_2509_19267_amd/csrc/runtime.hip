@@ -156,6 +156,7 @@ struct rgdbek_ctx {
   MergePlan csr_mp, csc_mp;   // nonzero-balanced full-pass plans
   RowGroups csr_rg, csc_rg;   // many right-hand sides: grouped rows
   double *rho = nullptr, *kappa = nullptr;
+  int rho_lost = 0, kappa_lost = 0;   // launch_recip_range of both
   Engine<double> e64;
   Engine<double> e64t;        // adjoint system (A^T), built on demand
   Engine<float> e32;          // inner engine of the mixed form
@@ -228,7 +229,7 @@ template <> Engine<float> &forward_engine<float>(rgdbek_ctx *h) { return h->e32;
 // Gram-block solve work (dense engines, and sparse engines small enough for
 // the Gram matrices of all columns and rows).
 template <typename T>
-void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e) {
+void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
   Pool &P = h->pool;
   e.GU = P.alloc<T>(e.kc * e.kc);
   if (!e.tall_rows) e.GJ = P.alloc<T>(e.kr * e.kr);
@@ -238,6 +239,8 @@ void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e) {
   e.s = P.alloc<T>(e.kr);
   for (CgWork<T> *cw : {&e.cgc, &e.cgr}) {
     const int64_t cap = (cw == &e.cgc) ? e.kc : e.kr;
+    const int lost = (cw == &e.cgc) != transpose ? h->kappa_lost : h->rho_lost;
+    cw->divide = (lost & (std::is_same<T, double>::value ? 1 : 2)) != 0;
     cw->cap = cap;
     cw->res = P.alloc<T>(cap);
     cw->p = P.alloc<T>(2 * cap);
@@ -329,7 +332,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       }
       e.aat = aat;
     }
-    alloc_gram_blocks(h, e);
+    alloc_gram_blocks(h, e, transpose);
     e.upd = P.alloc<T>(std::max(thin_update_scratch(e.m, e.kc),
                                 thin_update_scratch(e.n, e.kr)));
   } else {
@@ -544,7 +547,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       launch_gram_full<T>(rm, ld, e.m, e.n, F2, h->st);
       e.ata = F1;
       e.aat = F2;
-      alloc_gram_blocks(h, e);
+      alloc_gram_blocks(h, e, transpose);
       e.sgram = true;
     }
   }
@@ -700,7 +703,9 @@ struct IterOpts {
 };
 
 // Gram solve of a dense block projection: the persistent one-launch PCG when
-// the block fits it, else two launches per CG step.  With a
+// the block fits it, else two launches per CG step; these also where a squared
+// norm has no normal reciprocal, for they divide by it (in the persistent PCG
+// a choice between both costs 4-6 % of a 20000 x 5000 solve).  With a
 // precomputed full Gram F (leading dimension ldf) the block G is not yet
 // gathered: the persistent PCG reads it from F itself, the step-per-launch
 // form after a gather launch.  nrm: the full Gram's diagonal.
@@ -710,7 +715,7 @@ void pcg_solve(rgdbek_ctx *h, T *G, int64_t cap, const int64_t *cnt,
                CgWork<T> &w, int maxs, double itol, int ph,
                const T *F = nullptr, int64_t ldf = 0) {
   const bool f64 = std::is_same<T, double>::value;
-  if (pcg_persist_fits(cap, h->ncu, f64)) {
+  if (pcg_persist_fits(cap, h->ncu, f64) && !w.divide) {
     launch_pcg_persist<T>(G, cap, cnt, hsrc, hl, nrm, y, w,
                           pcg_persist_grid(cap, h->ncu), maxs, itol, h->ctrl,
                           ph, h->st, F, ldf);
@@ -1495,7 +1500,7 @@ void create_impl(rgdbek_ctx *h, const rgdbek_matrix *A) {
                        " are not supported unless taller than A is wide"};
   h->ctrl = P.alloc<Ctrl>(1);
   HIPCHK(hipHostMalloc((void **)&h->hctrl, sizeof(Ctrl), hipHostMallocDefault));
-  int *flag = P.alloc<int>(1);
+  int *flag = P.alloc<int>(3);
   if (h->dense) {
     h->ld = round_up(std::max<int64_t>(h->n, 1), 8);
     h->ldc = round_up(std::max<int64_t>(h->m, 1), 8);
@@ -1553,10 +1558,14 @@ void create_impl(rgdbek_ctx *h, const rgdbek_matrix *A) {
     launch_sqnorms_csr<double>(a, h->rho, st);
     launch_sqnorms_csr<double>(at, h->kappa, st);
   }
-  int hv = 0;
-  HIPCHK(hipMemcpyAsync(&hv, flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  launch_recip_range(h->rho, h->m, flag + 1, st);
+  launch_recip_range(h->kappa, h->n, flag + 2, st);
+  int hv[3] = {0, 0, 0};
+  HIPCHK(hipMemcpyAsync(hv, flag, sizeof(hv), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (hv) throw ApiError{RGDBEK_ERR_NUMERIC, "matrix values contain NaN/Inf"};
+  if (hv[0]) throw ApiError{RGDBEK_ERR_NUMERIC, "matrix values contain NaN/Inf"};
+  h->rho_lost = hv[1];
+  h->kappa_lost = hv[2];
   HIPCHK(hipStreamSynchronize(st));
 }
 

@@ -124,6 +124,28 @@ void launch_check_finite(const T *v, int64_t n, int *flag, hipStream_t st) {
                      dim3(256), 0, st, v, n, flag);
 }
 
+// Whether a squared norm that is not zero has a reciprocal that is not a
+// normal number, in FP64 (1) and in FP32 (2).
+template <typename T>
+__device__ __forceinline__ bool recip_lost(T v, T tiny) {
+  return (v > (T)0 && v < tiny) || (v > (T)1 / tiny && v - v == (T)0);
+}
+__global__ void recip_range_kernel(const double *__restrict__ v, int64_t n,
+                                   int *flag) {
+  int bad = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * 256) {
+    if (recip_lost(v[i], 0x1p-1022)) bad |= 1;
+    if (recip_lost((float)v[i], 0x1p-126f)) bad |= 2;
+  }
+  if (bad) atomicOr(flag, bad);
+}
+void launch_recip_range(const double *v, int64_t n, int *flag,
+                        hipStream_t st) {
+  hipLaunchKernelGGL(recip_range_kernel, dim3(grid_for(n, 256, 4096)),
+                     dim3(256), 0, st, v, n, flag);
+}
+
 // ------------------------------------------------------------ CSR -> CSC
 __global__ void col_count_kernel(int64_t nnz, const int32_t *__restrict__ ci,
                                  int64_t *__restrict__ cnt) {

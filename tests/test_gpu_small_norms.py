@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("e", [66, 69, 71])
 @pytest.mark.parametrize("k,solver,gram_aat", [
-    (200, "CHOL", False), (200, "CHOL", True), (400, "CHOL", True)])
+    (200, "CHOL", False), (200, "CHOL", True), (400, "CHOL", True),
+    (300, "CG", False), (600, "CG", True)])
 def test_mixed(e, k, solver, gram_aat):
     import paper_2509_19267_amd as rg
     m, n = 2000, 800
