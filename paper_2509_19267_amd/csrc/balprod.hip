@@ -189,7 +189,7 @@ bal_prod(Csr<T> A, const int32_t *__restrict__ off,
       if (blockIdx.x == 0 && tid == 0) ctrl->cg_done[0] = 1;
       return;
     }
-    alpha = (T)(ctrl->cg_rzp[0][step & 1] / qq);
+    alpha = qq > 0.0 ? (T)(ctrl->cg_rzp[0][step & 1] / qq) : (T)0;
   } else if (EPI == BP_COL_NARROW || EPI == BP_ROW_WIDE) {
     alpha = (T)ctrl->cg_alpha[PH];
   }

@@ -398,7 +398,7 @@ gc_col(const Team &team, const Csr<T> &W, int lgw, const Csr<T> &At, int lgt,
         }))
       return;
     if (qq == 0.0) break;
-    const double alpha = gam / qq;
+    const double alpha = qq > 0.0 ? gam / qq : 0.0;   // (not for a NaN)
     double ss;
     if (!ex.phase(ss, [&](int b, double &acc) {
           pw.share(b);

@@ -775,7 +775,7 @@ sc_narrow_col(Csr<T> At, const int32_t *__restrict__ U,
       if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->cg_done[0] = 1;
       return;
     }
-    alpha = ctrl->cg_rzp[0][step & 1] / qq;
+    alpha = qq > 0.0 ? ctrl->cg_rzp[0][step & 1] / qq : 0.0;
   } else {
     alpha = ctrl->cg_alpha[0];
   }
