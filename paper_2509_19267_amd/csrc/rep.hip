@@ -204,22 +204,24 @@ rep_rg_build(int64_t brows, const int64_t *__restrict__ ptr,
 }
 
 // Brings n entries into L2, a lane per 64 bytes (at most 16 KB): the scalar
-// loads that follow would each wait on HBM.  Returns whether a value is none
-// that a matrix holds (never: the loads need a use).
+// loads that follow would each wait on HBM.  What is returned must have a use
+// for the loads to stay, an empty statement at the sums (not a volatile one:
+// after that the values no longer come through the scalar cache).
 template <typename E>
-__device__ __forceinline__ bool rg_fetch(const E *p, int64_t n, int lane) {
+__device__ __forceinline__ unsigned rg_fetch(const E *p, int64_t n, int lane) {
   constexpr int PER = 64 / (int)sizeof(E);
-  bool odd = false;
+  unsigned x = 0;
   if (n > 4 * WAVE * PER) n = 4 * WAVE * PER;
   for (int64_t i = (int64_t)lane * PER; i < n; i += WAVE * PER)
-    odd |= !(p[i] - p[i] == (E)0);
-  return odd;
+    x ^= *reinterpret_cast<const unsigned *>(p + i);
+  return x;
 }
 
 // N columns of mask M, their indices in lanes j .. of ixv: the gathers in
 // flight together, then the multiply-adds.  Only the first n columns are
-// this mask's: the others, read past its end (valid columns, or the arrays'
-// padding), count as zero.
+// this mask's: of the others, read past its end (valid columns, or the
+// arrays' padding), gather and value count as zero, for either may be
+// infinite.
 template <int M, int N, typename T>
 __device__ __forceinline__ void rg_step(T (&acc)[REP_RG], const T *in,
                                         unsigned s, int ixv, int j,
@@ -233,7 +235,10 @@ __device__ __forceinline__ void rg_step(T (&acc)[REP_RG], const T *in,
     int k = u * __builtin_popcount(M);
 #pragma unroll
     for (int r = 0; r < REP_RG; ++r)
-      if (M >> r & 1) acc[r] += vx[k++] * x;
+      if (M >> r & 1) {
+        const T v = vx[k++];
+        acc[r] += (u < n ? v : (T)0) * x;
+      }
   }
 }
 // The n columns of mask M.  ixv: the first 64 of them, one per lane, loaded
@@ -297,7 +302,7 @@ rep_rg_kernel(int64_t brows, int64_t rep, const int64_t *__restrict__ ptr,
     const int32_t *n = cnt + g * RG_MASKS;
     const int64_t e1 = ptr[row + REP_RG < brows ? row + REP_RG : brows];
     int ixv = ix[lane];
-    if (rg_fetch(vx, e1 - e0, lane)) acc[0] = (T)1;
+    asm("" : "+v"(acc[0]) : "v"(rg_fetch(vx, e1 - e0, lane)));
     rg_mask<1>(acc, in, o, ix, vx, n[1], lane, ixv, R);
     rg_mask<2>(acc, in, o, ix, vx, n[2], lane, ixv, R);
     rg_mask<3>(acc, in, o, ix, vx, n[3], lane, ixv, R);
