@@ -237,7 +237,7 @@ __device__ __forceinline__ void rg_step(T (&acc)[REP_RG], const T *in,
     for (int r = 0; r < REP_RG; ++r)
       if (M >> r & 1) {
         const T v = vx[k++];
-        acc[r] += (u < n ? v : (T)0) * x;
+        acc[r] = fma(u < n ? v : (T)0, x, acc[r]);
       }
   }
 }
