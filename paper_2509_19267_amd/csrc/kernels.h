@@ -132,6 +132,7 @@ struct Csr {                 // CSR (or CSC viewed as CSR of the transpose)
   // second launch from per-chunk head/lead partials.
   const int32_t *mp_rs = nullptr;
   int64_t mp_nchunk = 0, mp_maxrows = 0;   // most rows of one chunk
+  int64_t mp_maxlen = 0;                   // most nonzeros of one row
   const int32_t *mp_xrow = nullptr, *mp_xcs = nullptr, *mp_xce = nullptr;
   int64_t mp_ncross = 0;
   T *mp_head = nullptr, *mp_lead = nullptr;   // nchunk each

@@ -19,7 +19,7 @@ constexpr int64_t MP_CH = 256;   // nonzeros per chunk
 // and last chunk.
 struct MergeRows {
   std::vector<int32_t> rs, xrow, xcs, xce;
-  int64_t nchunk = 0, maxrows = 0;
+  int64_t nchunk = 0, maxrows = 0, maxlen = 0;   // of a chunk; of a row
 };
 inline MergeRows merge_rows(const int64_t *rp, int64_t rows) {
   MergeRows p;
@@ -32,6 +32,7 @@ inline MergeRows merge_rows(const int64_t *rp, int64_t rows) {
   for (int64_t c = 0; c < p.nchunk; ++c)
     p.maxrows = std::max<int64_t>(p.maxrows, p.rs[c + 1] - p.rs[c]);
   for (int64_t r = 0; r < rows; ++r) {
+    p.maxlen = std::max<int64_t>(p.maxlen, rp[r + 1] - rp[r]);
     if (rp[r + 1] == rp[r]) continue;
     const int64_t cs = rp[r] / MP_CH, ce = (rp[r + 1] - 1) / MP_CH;
     if (ce > cs) {

@@ -1989,7 +1989,7 @@ Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
 // The block projections of one stored matrix with products balanced by
 // nonzeros.  wr and wc hold the block's entries by rows and by columns.
 //
-// Taken wherever a block has more than BAL_MIN_CAP indices, because it was
+// Taken where a block has more than BAL_MIN_CAP indices, because it was
 // faster over all of its range on power-law rows (8 iterations, row split /
 // balanced, ms): 10000 x 5000 at 1 % blocks 2.19 / 2.14 and at 50 % 4.13 /
 // 3.08, 100000 x 50000 at 10 % 4.83 / 3.24, 1M x 500K at 10 % 13.4 / 11.3 and
@@ -1997,8 +1997,14 @@ Csr<T> launch_sub_matrix(const Csr<T> &A, const int32_t *list,
 // all rows costs more than the block (3000 x 1500 at 1 %: 1.90 / 1.96).  Not
 // for even rows of 64 entries and more (no long segments), where a wave per
 // row is already balanced (40000 x 20000, 1 % dense: 208 / 219), nor where a
-// workgroup would get many thousand (empty) rows, which are not spread.
+// workgroup would get many thousand (empty) rows, which are not spread, nor
+// with longer rows or columns than BAL_MAX_LEN: one workgroup walks such a one
+// tile by tile, while the row split has a workgroup without tiles for it (50 %
+// blocks of 100000 x 100000 with 4 long rows, row split / balanced, ms: of
+// 4000 entries 5.37 / 4.93, of 16000 7.5 / 7.7, of 100000 21.6 / 28.6; with
+// 200 long rows of 4000 6.2 / 5.9, of 8000 8.0 / 8.3).
 constexpr int64_t BAL_MIN_CAP = 32;
+constexpr int64_t BAL_MAX_LEN = 4096;
 constexpr int64_t BAL_MAX_ROWS = 1024;         // of one chunk of the plan
 template <typename T>
 bool balanced_cg_takes(const Csr<T> &csr, const Csr<T> &csc, int64_t cap,
@@ -2008,6 +2014,7 @@ bool balanced_cg_takes(const Csr<T> &csr, const Csr<T> &csc, int64_t cap,
   if (csr.group == 64 && csc.group == 64 && !csr.nlong && !csc.nlong)
     return false;
   if (std::max(csr.mp_maxrows, csc.mp_maxrows) > BAL_MAX_ROWS) return false;
+  if (std::max(csr.mp_maxlen, csc.mp_maxlen) > BAL_MAX_LEN) return false;
   // the copies' and the partials' room
   const int64_t nb = bal_blocks(std::max(csr.mp_nchunk, csc.mp_nchunk));
   return nb + 4 * (int64_t)SC_SUM_MAX <= part_cap &&

@@ -54,7 +54,7 @@ int pick_group(double mean_len) {
 struct MergePlan {
   int32_t *rs = nullptr;                 // nchunk + 1 owned-row starts
   int32_t *xrow = nullptr, *xcs = nullptr, *xce = nullptr;
-  int64_t nchunk = 0, ncross = 0, maxrows = 0;
+  int64_t nchunk = 0, ncross = 0, maxrows = 0, maxlen = 0;
 };
 
 // Row groups of the many-right-hand-side products of one CSR (see rep.hip).
@@ -379,6 +379,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
         c.mp_rs = mp.rs;
         c.mp_nchunk = mp.nchunk;
         c.mp_maxrows = mp.maxrows;
+        c.mp_maxlen = mp.maxlen;
         c.mp_xrow = mp.xrow;
         c.mp_xcs = mp.xcs;
         c.mp_xce = mp.xce;
@@ -1469,6 +1470,7 @@ void build_merge_plan(rgdbek_ctx *h, const int64_t *ptr_dev, int64_t rows,
   const MergeRows p = merge_rows(rp.data(), rows);
   mp->nchunk = p.nchunk;
   mp->maxrows = p.maxrows;
+  mp->maxlen = p.maxlen;
   mp->ncross = (int64_t)p.xrow.size();
   auto up = [&](const std::vector<int32_t> &v) {
     int32_t *d = h->pool.alloc<int32_t>(std::max<int64_t>(1, (int64_t)v.size()), false);

@@ -18,6 +18,9 @@ extern "C" int64_t plan(const int64_t *rp, int64_t rows, int32_t *rs) {
   for (size_t c = 0; c < p.rs.size(); ++c) rs[c] = p.rs[c];
   return p.nchunk;
 }
+extern "C" int64_t longest(const int64_t *rp, int64_t rows) {
+  return rg::merge_rows(rp, rows).maxlen;
+}
 extern "C" int64_t first_row(int64_t rs, int64_t re, int64_t lane, int64_t rows) {
   return rg::mp_first_row(rs, re, lane, rows);
 }
@@ -31,7 +34,7 @@ def lib(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC,
                     str(d / "d.cpp"), "-o", str(d / "d.so")], check=True)
     so = ctypes.CDLL(str(d / "d.so"))
-    so.plan.restype = so.first_row.restype = ctypes.c_int64
+    so.plan.restype = so.first_row.restype = so.longest.restype = ctypes.c_int64
     so.first_row.argtypes = [ctypes.c_int64] * 4
     return so
 
@@ -50,6 +53,8 @@ def test_rows_loaded_ahead_exist(lib, name):
     rs = np.full(max(1, (nnz + 255) // 256) + 1, -1, np.int32)
     nchunk = lib.plan(ctypes.c_void_p(rp.ctypes.data), ctypes.c_int64(rows),
                       ctypes.c_void_p(rs.ctypes.data))
+    assert lib.longest(ctypes.c_void_p(rp.ctypes.data),
+                       ctypes.c_int64(rows)) == max(LENS[name])
     assert nchunk == len(rs) - 1 and rs[0] == 0 and rs[-1] == rows
     for c in range(nchunk):
         for r in range(rs[c], rs[c + 1]):
