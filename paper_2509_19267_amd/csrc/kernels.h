@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "mergeplan.h"
+#include "repgroups.h"
 
 namespace rg {
 
@@ -580,14 +581,13 @@ constexpr int64_t REP_MM_MIN = 16;
 template <typename T>
 int launch_rep_mm(const Csr<T> &A, const T *in, T *out, double *part,
                   Ctrl *ctrl, int ph, int respect_done, hipStream_t st);
-// Row groups of the product: table entries for a matrix of brows rows, and
-// whether they pay (columns gathered by all groups against stored entries).
+// Row groups of the product (repgroups.h): table entries for a matrix of brows
+// rows.
 // The build counts first (gidx null: cnt, and the columns into *total, which
 // starts at zero), then fills gidx and gval (nnz entries each, and
 // rep_rg_pad() zeros after them, which the product may read).
 int64_t rep_rg_table(int64_t brows);
 int64_t rep_rg_pad();
-bool rep_rg_pays(int64_t cols, int64_t nnz);
 template <typename T>
 void launch_rep_rg_build(const Csr<T> &A, int32_t *cnt,
                          unsigned long long *total, int32_t *gidx, T *gval,

@@ -104,14 +104,11 @@ rep_mm_kernel(Csr<T> A, const T *__restrict__ in, T *__restrict__ out,
 // those rows in the index and value arrays; its columns of mask 1 come
 // first, then mask 2, ..., ascending within a mask, with the values of the
 // rows holding a column side by side; counts per mask in 16 ints.
-// Taken when a group's columns are at most REP_RG_SHARE of its entries: below
-// that the loads saved outweigh the shorter straight loops.  Measured on the
-// 256^2 blur (15 x 15 entries, 0.30 of the gathers left), 64 right-hand
-// sides, a product (mean of A and A^T): FP32 184 -> 83 us; A x and A^T z with
+// Taken by the rule of repgroups.h.  Measured on the 256^2 blur (15 x 15
+// entries, 0.30 of the gathers left), 64 right-hand sides, a product (mean of A and A^T): FP32 184 -> 83 us; A x and A^T z with
 // their transposes 482 -> 260 us in FP32, 1019 -> 466 us in FP64.
 constexpr int REP_RG = 4;
 constexpr int RG_MASKS = 1 << REP_RG;
-constexpr double REP_RG_SHARE = 0.6;
 // Columns gathered together (16 lengthen the waits on the values: 85 against
 // 83 us in FP32; 4 in FP64: no change).
 constexpr int RG_UNR = 8;
@@ -336,9 +333,6 @@ rep_rg_kernel(int64_t brows, int64_t rep, const int64_t *__restrict__ ptr,
 int64_t rep_rg_pad() { return WAVE * REP_RG; }
 int64_t rep_rg_table(int64_t brows) {
   return (brows + REP_RG - 1) / REP_RG * RG_MASKS;
-}
-bool rep_rg_pays(int64_t cols, int64_t nnz) {
-  return (double)cols <= REP_RG_SHARE * (double)nnz;
 }
 template <typename T>
 void launch_rep_rg_build(const Csr<T> &A, int32_t *cnt,

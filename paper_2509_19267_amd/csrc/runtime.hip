@@ -403,6 +403,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
     // neighbouring rows share enough columns
     if (h->rep > 32) {
       auto groups = [&](Csr<T> &c, RowGroups &rg) {
+        if (!rep_rg_fits(h->rep, h->nnz, h->ncu, f64)) return;
         if (!rg.cnt) {
           rg.cnt = P.alloc<int32_t>(rep_rg_table(c.brows), false);
           unsigned long long *tot = P.alloc<unsigned long long>(1), hv = 0;
