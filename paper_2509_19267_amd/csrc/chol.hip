@@ -127,36 +127,40 @@ __device__ __forceinline__ T diag_max(const T *G, int64_t ldg, int c, T *wmax) {
 
 // ------------------------------------------------------------ up to 256
 constexpr int CR_MAX = 256;
-constexpr int CR_NT = 1024;
-constexpr int CR_NW = CR_NT / WAVE;
-constexpr int CR_T = CR_MAX / CH_B;
-constexpr int CR_OWN =
-    (CR_T * (CR_T + 1) / 2 + CR_NW - 2) / (CR_NW - 1);   // tiles per wave
-constexpr int64_t CR_TILES = (int64_t)(CR_NW - 1) * CR_OWN * CH_B * CH_B;
+// One tile (blocks up to 16) needs one wave beside wave 0: 16 of them made a
+// solve of one index in a 300 x 300 system 6 % slower than a thread per row.
+template <int M> struct CrShape {
+  static constexpr int nt = M <= CH_B ? 2 * WAVE : 1024, nw = nt / WAVE;
+  static constexpr int t = M / CH_B;
+  static constexpr int own = (t * (t + 1) / 2 + nw - 2) / (nw - 1);  // per wave
+  static constexpr int64_t tiles = (int64_t)(nw - 1) * own * CH_B * CH_B;
+};
 
-template <typename T>
-__global__ void __launch_bounds__(CR_NT, 4)
+template <typename T, int M>
+__global__ void __launch_bounds__(CrShape<M>::nt, M <= CH_B ? 1 : 4)
 chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
                 const int64_t *__restrict__ cnt, const T *__restrict__ hsrc,
                 const int32_t *__restrict__ hl, T *__restrict__ y,
                 T *__restrict__ W, int factor, const Ctrl *ctrl) {
   if (ctrl_done(ctrl)) return;
+  constexpr int NT = CrShape<M>::nt, NW = CrShape<M>::nw;
+  constexpr int OWN = CrShape<M>::own;
   typedef typename Mfma16<T>::v4 v4;
   const int c = (int)*cnt;
   if (c <= 0) return;
-  __shared__ T pan[2][CR_MAX * CH_P];
-  __shared__ T li[CR_T][CH_B * CH_P];          // inverses of the diagonal tiles
-  __shared__ T vec[CR_MAX], vs[CR_MAX], ys[CR_MAX];
+  __shared__ T pan[2][M * CH_P];
+  __shared__ T li[CrShape<M>::t][CH_B * CH_P];          // inverses of the diagonal tiles
+  __shared__ T vec[M], vs[M], ys[M];
   __shared__ T zero[CH_B * CH_P];
-  __shared__ T wmax[CR_NW];
+  __shared__ T wmax[NW];
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int lr = lane & 15, lk = lane >> 4;
   const int nt = (c + CH_B - 1) / CH_B;
-  if (tid < CR_MAX)
+  if (tid < M)
     vec[tid] = tid < c ? (hl ? hsrc[hl[tid]] : hsrc[tid]) : (T)0;
-  for (int e = tid; e < CH_B * CH_P; e += CR_NT) zero[e] = (T)0;
-  T *wi = W + CR_TILES;
+  for (int e = tid; e < CH_B * CH_P; e += NT) zero[e] = (T)0;
+  T *wi = W + CrShape<M>::tiles;
   T thr = (T)0;
   // The block is factored as sc G, sc a power of 4 that takes its largest
   // diagonal entry near 1 (denormal ones to 2^-25), so that the pivots above
@@ -164,17 +168,17 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
   // bits as without).
   T sc = (T)1;
   if (factor) {
-    const T mx = diag_max<CR_NT, T>(G, ldg, c, wmax);
+    const T mx = diag_max<NT, T>(G, ldg, c, wmax);
     int ex = 0;
     if (mx > (T)0 && mx <= std::numeric_limits<T>::max()) (void)frexp(mx, &ex);
     constexpr int lim = std::numeric_limits<T>::max_exponent - 4;
     ex = (ex < -lim ? -lim : ex > lim ? lim : ex) & ~1;
     sc = ldexp((T)1, -ex);
     thr = mx * sc * (T)1e-13;
-    if (tid == 0) wi[CR_MAX * CH_B] = sc;
+    if (tid == 0) wi[M * CH_B] = sc;
   } else {
-    sc = wi[CR_MAX * CH_B];
-    for (int e = tid; e < nt * CH_B * CH_B; e += CR_NT)
+    sc = wi[M * CH_B];
+    for (int e = tid; e < nt * CH_B * CH_B; e += NT)
       li[e / (CH_B * CH_B)][e / CH_B % CH_B * CH_P + e % CH_B] = wi[e];
   }
   // the 16 unknowns of a panel, lane l holding that of row l % 16: forward
@@ -207,10 +211,18 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
 #pragma unroll
       for (int k = 0; k < CH_B; ++k) x[k] = cur[lr * CH_P + k];
       T r = pivot_recip<0>(x, dv, thr, lr);
-      auto steps = [&]<int... J>(std::integer_sequence<int, J...>) {
-        (pivot_step<J>(x, r, dv, thr, lr), ...);
+      // (in fours: the last panel ends with the block, which leaves a block
+      // of a few columns a few pivots)
+      const int left = c - p * CH_B;
+      auto steps = [&]<int J0, int... J>(std::integral_constant<int, J0>,
+                                         std::integer_sequence<int, J...>) {
+        if (left > J0) (pivot_step<J0 + J>(x, r, dv, thr, lr), ...);
       };
-      steps(std::make_integer_sequence<int, CH_B>{});
+      constexpr auto four = std::make_integer_sequence<int, 4>{};
+      steps(std::integral_constant<int, 0>{}, four);
+      steps(std::integral_constant<int, 4>{}, four);
+      steps(std::integral_constant<int, 8>{}, four);
+      steps(std::integral_constant<int, 12>{}, four);
       const T iv = dv > thr ? rsqrt(dv) : (T)0;
       if (lane < CH_B)
 #pragma unroll
@@ -235,22 +247,23 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
     }
   } else {
     // the wave's tiles: columns 0, 1, ... in turn, dealt to the other waves
-    v4 acc[CR_OWN];
-    int ti[CR_OWN], tj[CR_OWN];
-    T *wt = W + (int64_t)(wv - 1) * CR_OWN * CH_B * CH_B + lane;
+    v4 acc[OWN];
+    int ti[OWN], tj[OWN];
+    T *wt = W + (int64_t)(wv - 1) * OWN * CH_B * CH_B + lane;
     {
       int j = 0, o = wv - 1;
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s) {
+      for (int s = 0; s < OWN; ++s) {
         while (j < nt && o >= nt - j) { o -= nt - j; ++j; }
         ti[s] = j + o;
         tj[s] = j;        // nt: no tile
-        o += CR_NW - 1;
+        o += NW - 1;
       }
     }
     if (factor) {
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s) {
+      for (int s = 0; s < OWN; ++s) {
+        if (tj[s] >= nt) break;
         const int k = tj[s] * CH_B + lr;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -262,15 +275,17 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s) acc[s] *= sc;
+      for (int s = 0; s < OWN; ++s) acc[s] *= sc;
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s)
         if (tj[s] == 0) tile_put<T>(acc[s], &pan[0][ti[s] * CH_B * CH_P]);
     } else {
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s) {
+        if (tj[s] >= nt) break;
 #pragma unroll
         for (int u = 0; u < 4; ++u) acc[s][u] = wt[(s * 4 + u) * WAVE];
+      }
     }
     __syncthreads();
     for (int p = 0; factor && p < nt; ++p) {
@@ -278,7 +293,7 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
       // panel p - 1's product from the tiles right of panel p
       if (p > 0) {
 #pragma unroll
-        for (int s = 0; s < CR_OWN; s += 2) {
+        for (int s = 0; s + 1 < OWN; s += 2) {
           // two tiles at once; one that is done takes the zero tile
           if (tj[s + 1] <= p || tj[s] >= nt) continue;
 #pragma unroll
@@ -294,7 +309,7 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
       __syncthreads();
       // the panel's tiles below the diagonal, times the inverse
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s)
         if (tj[s] == p && ti[s] > p) {
           T *t = &cur[(ti[s] - p) * CH_B * CH_P];
           acc[s] = (v4){0, 0, 0, 0};
@@ -304,7 +319,7 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
       __syncthreads();
       // panel p's product completes panel p + 1
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s)
         if (tj[s] == p + 1 && tj[s] < nt) {
           tile_mma<T>(acc[s], &cur[(ti[s] - p) * CH_B * CH_P],
                       &cur[CH_B * CH_P], (T)-1);
@@ -314,15 +329,17 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
     }
     if (factor) {
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s) {
+        if (tj[s] >= nt) break;
 #pragma unroll
         for (int u = 0; u < 4; ++u) wt[(s * 4 + u) * WAVE] = acc[s][u];
+      }
     }
     // forward: vec_i -= L_ip v_p below panel p
     for (int p = 0; p < nt; ++p) {
       const T v = forward(p);
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s)
         if (tj[s] == p && ti[s] > p) {
           T x = fold_dpp<DPP_ROR8>(acc[s][0] * v, acc[s][1] * v, (lr & 8) != 0);
           const T z = fold_dpp<DPP_ROR8>(acc[s][2] * v, acc[s][3] * v,
@@ -343,7 +360,7 @@ chol_reg_kernel(const T *__restrict__ G, int64_t ldg,
 #pragma unroll
       for (int u = 0; u < 4; ++u) yr[u] = __shfl(v, Mfma16<T>::row(lk, u), WAVE);
 #pragma unroll
-      for (int s = 0; s < CR_OWN; ++s)
+      for (int s = 0; s < OWN; ++s)
         if (ti[s] == p && tj[s] < p) {
           T x = acc[s][0] * yr[0] + acc[s][1] * yr[1] + acc[s][2] * yr[2] +
                 acc[s][3] * yr[3];
@@ -563,16 +580,28 @@ chol_big_kernel(T *__restrict__ G, int64_t ldg,
 }
 
 int64_t chol_work_size(int64_t cap) {
-  return cap <= CR_MAX ? CR_TILES + CR_MAX * CH_B + 1 : 1;
+  auto size = [](auto m) {
+    constexpr int M = decltype(m)::value;
+    return CrShape<M>::tiles + M * CH_B + 1;
+  };
+  if (cap > CR_MAX) return 1;
+  return cap > CH_B ? size(std::integral_constant<int, CR_MAX>{})
+                    : size(std::integral_constant<int, CH_B>{});
 }
 
 template <typename T>
 void launch_chol_solve(T *G, int64_t cap, const int64_t *count_dev,
                        const T *hsrc, const int32_t *hlist, T *y, T *W,
                        int factor, Ctrl *ctrl, hipStream_t st) {
-  if (cap <= CR_MAX)
-    hipLaunchKernelGGL(chol_reg_kernel<T>, dim3(1), dim3(CR_NT), 0, st,
-                       (const T *)G, cap, count_dev, hsrc, hlist, y, W, factor,
+  if (cap <= CH_B)
+    hipLaunchKernelGGL((chol_reg_kernel<T, CH_B>), dim3(1),
+                       dim3(CrShape<CH_B>::nt), 0, st, (const T *)G, cap,
+                       count_dev, hsrc, hlist, y, W, factor,
+                       (const Ctrl *)ctrl);
+  else if (cap <= CR_MAX)
+    hipLaunchKernelGGL((chol_reg_kernel<T, CR_MAX>), dim3(1),
+                       dim3(CrShape<CR_MAX>::nt), 0, st, (const T *)G, cap,
+                       count_dev, hsrc, hlist, y, W, factor,
                        (const Ctrl *)ctrl);
   else
     hipLaunchKernelGGL(chol_big_kernel<T>, dim3(1), dim3(CH_NT), 0, st, G, cap,
