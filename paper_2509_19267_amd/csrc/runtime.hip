@@ -249,10 +249,11 @@ void alloc_gram_blocks(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
     cw->pv = P.alloc<double>(cap / 4 + 64);
     cw->part_cap = cap / 256 + 2;
     cw->part = P.alloc<double>(4 * cw->part_cap);
-    cw->rzs = P.alloc<double>(2);
     cw->xch = P.alloc<T>(3 * cap, false);
-    cw->seq = P.alloc<unsigned>(1);
-    cw->team = P.alloc<unsigned long long>(2);
+    // one allocation for the few words of both PCGs
+    cw->rzs = P.alloc<double>(8);
+    cw->team = reinterpret_cast<unsigned long long *>(cw->rzs + 2);
+    cw->seq = reinterpret_cast<unsigned *>(cw->rzs + 4);
   }
 }
 
@@ -405,17 +406,21 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       auto groups = [&](Csr<T> &c, RowGroups &rg) {
         if (!rep_rg_fits(h->rep, h->nnz, h->ncu, f64)) return;
         if (!rg.cnt) {
-          rg.cnt = P.alloc<int32_t>(rep_rg_table(c.brows), false);
-          unsigned long long *tot = P.alloc<unsigned long long>(1), hv = 0;
+          // the counts, and before them the columns of all groups
+          unsigned long long *tot = P.alloc<unsigned long long>(
+              1 + rep_rg_table(c.brows) / 2), hv = 0;
+          rg.cnt = reinterpret_cast<int32_t *>(tot + 1);
           launch_rep_rg_build<T>(c, rg.cnt, tot, nullptr, nullptr, h->st);
           HIPCHK(hipMemcpyAsync(&hv, tot, sizeof(hv), hipMemcpyDeviceToHost,
                                 h->st));
           HIPCHK(hipStreamSynchronize(h->st));
           rg.pays = rep_rg_pays((int64_t)hv, h->nnz);
-          if (rg.pays) rg.idx = P.alloc<int32_t>(h->nnz + rep_rg_pad());
         }
         if (!rg.pays) return;
-        T *v = P.alloc<T>(h->nnz + rep_rg_pad());
+        // values, and behind them the indices that all precisions share
+        const int64_t len = h->nnz + rep_rg_pad();
+        T *v = P.alloc<T>(len + (rg.idx ? 0 : len * 4 / (int64_t)sizeof(T) + 1));
+        if (!rg.idx) rg.idx = reinterpret_cast<int32_t *>(v + len);
         launch_rep_rg_build<T>(c, rg.cnt, nullptr, rg.idx, v, h->st);
         c.rg_cnt = rg.cnt;
         c.rg_idx = rg.idx;
@@ -503,21 +508,35 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
       share = e.m ? (double)e.kr / (double)e.m : 1.0;
       sub(e.subr, at, capr, e.m);
     }
+    // Small single systems: the Gram matrices of all columns and all rows,
+    // formed once through a dense copy, turn each block projection into a
+    // gather, one Cholesky or persistent PCG launch and one sparse update,
+    // instead of two launches per CG step.
+    // (worth it when the projections are solved to the FP64 floor, i.e. many
+    // CG steps; with a loose inner tolerance a few matrix-free CG steps cost
+    // less than the gather)
+    const bool exact_inner = !(h->p.inner_tol > 1e-6);
+    const bool sgram = !(h->p.flags & RGDBEK_FLAG_SPARSE_CG) && h->rep == 1 &&
+                       h->nseg == 0 && exact_inner && e.m <= SPARSE_GRAM_MAX &&
+                       e.n <= SPARSE_GRAM_MAX;
+    // the matrix-free projections, which small systems use for tall row blocks
+    const bool free_cg = e.subc.idx && e.subr.idx &&
+                         !(h->p.flags & RGDBEK_FLAG_CG_SPLIT) &&
+                         (!sgram || e.tall_rows);
     // one launch per projection where the segments fit the compute units
     // (with the block copies: the products take no entry off the block)
-    if (e.subc.idx && e.subr.idx && !(h->p.flags & RGDBEK_FLAG_CG_SPLIT) &&
-        grid_cg_takes<T>(a, at, h->ncu)) {
-      const int64_t len = std::max(e.m, e.n) + 64;
-      e.gcg.q = P.alloc<T>(len);
-      e.gcg.sp = P.alloc<T>(2 * len);
-      if (e.tall_rows) e.gcg.rq = P.alloc<T>(2 * len);
-      e.gcg.part = P.alloc<double>(24 * h->ncu, false);
-      e.gcg.seq = P.alloc<unsigned>(2);
-      e.gcg.team = P.alloc<unsigned long long>(4);
+    if (free_cg && grid_cg_takes<T>(a, at, h->ncu)) {
+      const int64_t len = round_up(std::max(e.m, e.n), 32) + 64;
+      e.gcg.sp = P.alloc<T>((e.tall_rows ? 5 : 3) * len);
+      e.gcg.q = e.gcg.sp + 2 * len;
+      if (e.tall_rows) e.gcg.rq = e.gcg.sp + 3 * len;
+      e.gcg.part = P.alloc<double>(24 * h->ncu + 8);
+      e.gcg.team =
+          reinterpret_cast<unsigned long long *>(e.gcg.part + 24 * h->ncu);
+      e.gcg.seq = reinterpret_cast<unsigned *>(e.gcg.part + 24 * h->ncu + 4);
     }
     // larger ones: products balanced by nonzeros
-    if (e.subc.idx && e.subr.idx && !(h->p.flags & RGDBEK_FLAG_CG_SPLIT) &&
-        !e.gcg.q) {
+    if (free_cg && !e.gcg.q) {
       e.bal_c = balanced_cg_takes<T>(a, at, e.kc, e.scc.part_cap);
       e.bal_r = !e.tall_rows &&
                 balanced_cg_takes<T>(a, at, e.kr, e.scr.part_cap);
@@ -529,16 +548,7 @@ void build_engine(rgdbek_ctx *h, Engine<T> &e, bool transpose) {
         HIPCHK(hipMemsetAsync(sc.pos, 0xff, sizeof(int32_t) * d, h->st));
       }
     }
-    // Small single systems: the Gram matrices of all columns and all rows,
-    // formed once through a dense copy, turn each block projection into a
-    // gather, one Cholesky or persistent PCG launch and one sparse update,
-    // instead of two launches per CG step.
-    // (worth it when the projections are solved to the FP64 floor, i.e. many
-    // CG steps; with a loose inner tolerance a few matrix-free CG steps cost
-    // less than the gather)
-    const bool exact_inner = !(h->p.inner_tol > 1e-6);
-    if (!(h->p.flags & RGDBEK_FLAG_SPARSE_CG) && h->rep == 1 && h->nseg == 0 &&
-        exact_inner && e.m <= SPARSE_GRAM_MAX && e.n <= SPARSE_GRAM_MAX) {
+    if (sgram) {
       const int64_t ld = round_up(e.n, 8), ldc = round_up(e.m, 8);
       T *rm = P.alloc<T>(e.m * ld);
       T *cm = P.alloc<T>(e.n * ldc);
