@@ -449,7 +449,7 @@ gc_col_kernel(Csr<T> W, int lgw, Csr<T> At, int lgt, const int32_t *U,
 
 // ------------------------------------------------------------ rows
 // W: the block's entries by columns (indices: rows of A); A: all rows.
-//   phase 1: u = A^J^T p;  phase 2: v = A^J u, <p, v>;
+//   phase 1: u = A^J^T p;  phase 2: v = A^J u, <p, v>, <p, rho p>;
 //   phase 3: x += alpha u, res -= alpha v, zz = res / rho
 template <typename T, bool FULL>
 __device__ __forceinline__ void
@@ -492,6 +492,13 @@ gc_row(const Team &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
         pw.own([&](int k, int j) { if (k >= 0) xk[k] = x[j]; });
       }))
     return;
+  // A block of dependent rows that contradict each other leaves a residual
+  // that A^J^T does not see; the direction turns into it, and <p, A A^T p> into
+  // the square of a rounding error.  Below this part of its bound no step is
+  // taken and the CG ends.  (A zero there, which ended it before, depends on
+  // the order of the sums: with each of 5 rows 4 times, 10 iterations, 4 of 60
+  // solves ended in infinity.)
+  constexpr double GC_NULL = sizeof(T) == 8 ? 0x1p-98 : 0x1p-44;
   double beta = 0.0;
   int t = 0;
   const bool run = rr0 != 0.0 && c > 0;
@@ -513,16 +520,21 @@ gc_row(const Team &team, const Csr<T> &W, int lgw, const Csr<T> &A, int lga,
           });
         }))
       return;
-    if (!ex.phase(pv, [&](int b, double &acc) {
+    double pp;
+    if (!ex.phase2(pv, pp, [&](int b, double &a0, double &a1) {
           pa.share(b);
           pa.run([&](int32_t i) { return ld_agent(&u[i]); },
                  [&](int k, int a, T y) {
                    if (k >= 0) vk[k] = y;
                    else v[a] = y;
-                   acc += (double)y * (double)(k >= 0 ? pk[k] : dir(J[a]));
+                   const double pa = (double)(k >= 0 ? pk[k] : dir(J[a]));
+                   a0 += (double)y * pa;
+                   a1 += (k >= 0 ? dk[k] : rho[J[a]]) * pa * pa;
                  });
         }))
       return;
+    // a direction that the rows do not see beyond rounding (the residual of a
+    if (pv <= GC_NULL * pp) pv = 0.0;
     const double alpha = pv != 0.0 ? rz / pv : 0.0;
     double rz1, rr;
     if (!ex.phase2(rz1, rr, [&](int b, double &a0, double &a1) {
