@@ -145,7 +145,8 @@ enum { RGDBEK_SOLVER_AUTO = 0, RGDBEK_SOLVER_CHOL = 1, RGDBEK_SOLVER_CG = 2 };
  * are then gathered from these matrices instead of formed from A;
  * CG_SPLIT makes the sparse block projections finish every CG step with
  * separate many-workgroup launches whatever the block size (by default the
- * whole CG of a single system of moderate size is one launch, and otherwise
+ * whole CG of one stored matrix -- a single system or a batch -- of moderate
+ * size is one launch, its products are balanced by nonzeros, and otherwise
  * only blocks of more than 16384 indices do; smaller ones finish in the last
  * workgroup of the step).  The arithmetic is the same either way.
  * SPARSE_CG keeps the matrix-free CG projections for small sparse single

@@ -253,7 +253,7 @@ template <typename T>
 void launch_err_ref(int64_t n, const T *x, const double *x_ref,
                     const double *x_base, Reduce &red, Ctrl *ctrl,
                     int respect_done, hipStream_t st);
-// Ctrl::ref2 = sum v_i^2 (FP64), one workgroup.
+// Ctrl::ref2 = sum v_i^2 (FP64), partials in block order.
 template <typename T>
 void launch_set_ref2(int64_t n, const T *v, double *part, Ctrl *ctrl,
                      hipStream_t st);   // part: 1024

@@ -32,15 +32,15 @@
 // of that buffer then; the clear has landed (vmcnt wait) before the same
 // wave publishes step s + 1, without which nobody reads step s + 2.  That
 // holds because every workgroup that reads also publishes: those without a
-// row leave at once (pcgshare.h).  The rotation goes on across launches
-// (seq, read before the first publish and written after the last).  Polls are bounded: a timed-out
-// wait raises Ctrl::sync_fail, which ends the other waits, so the launch
-// always drains.
+// row leave at once (pcgshare.h).  The rotation goes on across launches (seq,
+// read before the first publish and written after the last).  Polls are
+// bounded: a timed-out wait raises Ctrl::sync_fail, which ends the other
+// waits, so the launch always drains.
 // Measured per launch, against the same CG with the block re-read from
 // memory each step and a counter barrier between the workgroups: FP64 4000
-// (mean of column and row blocks, 5 and 8 steps) 328 -> 153 us, most of it
+// (mean of column and row blocks, 5 and 8 steps) 328 -> 150 us, most of it
 // now the gather of the block from the full Gram; FP64 301 (about 40 steps)
-// 319 -> 106 us, 2.5 us per step; FP64 750 (exact) 109 us.
+// 319 -> 106 us, 2.5 us per step; FP64 750 (exact) 111 us.
 #include "common.h"
 #include "kernels.h"
 #include "lanes.h"

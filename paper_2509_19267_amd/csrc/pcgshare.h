@@ -6,8 +6,8 @@
 namespace rg {
 
 // Of a block of c rows, workgroup w of `active` has rows [w rpw, (w+1) rpw)
-// and clears entries [w per, (w+1) per) of a buffer of cap.  The launch's P
-// workgroups come from the block's capacity, c is known only on the device:
+// and clears entries [w per, (w+1) per) of a buffer of cap.  P, the workgroups
+// that are there, comes from the block's capacity, c only from the device:
 // those that are left without a row (6 of 256 at c = 4000, nearly all when
 // few weights are positive) take no part in the exchange, for nobody would
 // wait for them.  An empty block is one workgroup's.

@@ -170,8 +170,10 @@ constexpr int GS_W = 4;              // waves per tile
 constexpr int GS_DEPTH = 4;
 // Whole solves with the 64 x 64 tiles / these: 500 x 250 systems 38.9 / 33.8
 // ms, 2003 x 501 in blocks of 175 76.6 / 66.3, 4000 x 1000 of 350 93.3 / 76.9
-// and of 600 59.9 / 51.7.  Blocks of 2000 read their rows too often: 13.4 /
-// 12.0 ms at length 2500, but 27.2 / 29.6 at 6000.
+// and of 600 59.9 / 51.7.  Up to 1024 rows at every length (10 row blocks of
+// 512 at length 20000 23.8 / 6.9 ms, of 1000 23.7 / 18.1, at 60000 67.0 / 52.3,
+// in FP32 59.4 / 37.5); blocks of 2000 read their rows too often: 13.4 / 12.0 ms
+// at length 2500, but 27.2 / 29.6 at 6000.
 constexpr int64_t GS_MAX = 1024;
 template <typename T>
 __global__ void __launch_bounds__(GS_W * WAVE)
